@@ -273,9 +273,7 @@ int wilson_gauge_free(wilson_ctx *ctx, wilson_gauge *g) {
     API_BEGIN
     WL_CHECK_ARG(ctx != nullptr && g != nullptr, "ctx / g is NULL");
     WL_HIP(hipStreamSynchronize(ctx->stream));
-    // the dslash workspace key names this field; solve workspaces take the field per call
-    ctx->dslash_ws.reset();
-    ctx->dslash_key.clear();
+    ctx->dslash_ws.reset();  // (its memory goes back with the field's; solve workspaces stay)
     delete g;
     return WILSON_OK;
     API_END
@@ -368,7 +366,6 @@ int wilson_dslash(double *out, const double *in, const double *U, double kappa, 
         throw;
     }
     ctx->dslash_ws.reset();
-    ctx->dslash_key.clear();
     delete G;
     return WILSON_OK;
     API_END

@@ -222,6 +222,26 @@ int hop_nblocks(const HopArgs &a, const LaunchCfg &c);
 hipError_t launch_hop(const HopArgs &a, const LaunchCfg &c, hipStream_t s);
 bool hop_cfg_valid(const HopArgs &a, const LaunchCfg &c);
 
+// The operator call: out = D in (par 2) or the parity hop (par 0, 1; small kernel only), with
+// the output in the canonical layout.
+struct FullArgs {
+    Geom g;
+    int par;
+    int nrhs;
+    Spinor f[2];         // full kernel: the input's parity planes
+    const double2 *in;   // small kernel: the canonical input
+    const void *gauge;
+    int gprec, recon;
+    double cH;           // -kappa
+    double2 *out;
+};
+// plane blocks of the full kernel (0: memory order)
+inline int full_zblk(const Geom &g) {
+    return g.L[2] % 8 == 0 && (g.Lxh * g.L[1]) % 128 == 0 ? g.L[2] / 8 : 0;
+}
+hipError_t launch_dslash_full(const FullArgs &p, hipStream_t s);
+hipError_t launch_dslash_small(const FullArgs &p, int sp, hipStream_t s);
+
 // A finalize run at the start of a vector kernel instead of a launch of its own (short
 // partial rows only): the scalar step `op` on the `nv` values of each right-hand side's
 // `nblocks` partials, applied to the states `src` (phases in run_mask) and stored, with
@@ -270,10 +290,12 @@ hipError_t launch_finalize(int op, const double *partials, int nvals, int nblock
 hipError_t launch_zero(const Spinor &f, const Geom &g, int nrhs, hipStream_t s);
 
 // Layout / precision conversion.
-// canonical complex128 [rhs][V][4][3]  <->  parity field of precision f.prec.
-hipError_t launch_to_parity(Spinor f, const double *canon, const Geom &g, int par, int nrhs, double scale,
-                            hipStream_t s);
-hipError_t launch_from_parity(double *canon, Spinor f, const Geom &g, int par, int nrhs, hipStream_t s);
+// canonical complex128 [rhs][V][4][3]  <->  parity fields of precision f.prec: both parities
+// in one pass (split, join), or one of them.
+hipError_t launch_split(Spinor fe, Spinor fo, const double *canon, const Geom &g, int nrhs, hipStream_t s);
+hipError_t launch_split_one(Spinor f, const double *canon, const Geom &g, int par, int nrhs, hipStream_t s);
+hipError_t launch_join(double *canon, Spinor fe, Spinor fo, const Geom &g, int nrhs, hipStream_t s);
+hipError_t launch_join_one(double *canon, Spinor f, const Geom &g, int par, int nrhs, hipStream_t s);
 // dst (prec) = scale * src (FP64 parity field); nrhs fields; scale per rhs from state->aux if use_state.
 hipError_t launch_convert(Spinor dst, Spinor src, const Geom &g, int nrhs, const RhsState *state, int inv_sqrt_aux,
                           hipStream_t s);

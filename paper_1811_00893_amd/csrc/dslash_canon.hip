@@ -1,0 +1,259 @@
+// D = 1 - kappa H on both parities in one launch, with the output in the canonical layout
+// (the operator call; the solvers stay on parity planes).
+//
+// Two parity hops in separate launches read every link twice from HBM (each link serves the
+// forward hop of one parity and the backward hop of the other) and leave the result in
+// planes for another pass to put together.  Here one launch walks both parities of the same
+// sites together: the second use of a link, and the identity term, which is the site the
+// other parity's stencil is centred on, come from the caches, and a block's result leaves
+// as whole canonical rows through LDS.
+//
+// Two kernels:
+//   dslash_full_kernel   from parity planes (large lattices: bound by HBM);
+//   dslash_small_kernel  from the canonical input itself, five waves per 64 output sites as
+//                        in the solvers' direction split (lattices whose fields fit the
+//                        caches: the call is bound by launches and latency, and one launch
+//                        does what took a conversion of each parity, two hops and two
+//                        conversions back).
+#include "dslash_kernels.h"
+
+namespace wl {
+
+// What the gather helpers of the hop read of their argument struct.
+struct HopSource {
+    Spinor in;
+    const void *gauge;
+};
+
+// o as it reads back from storage precision SP (FP16: scaled by the site's largest component)
+template <int SP, typename R>
+__device__ __forceinline__ void as_stored(Cx<R> (&o)[12]) {
+    if constexpr (SP == P16) {
+        float s = 0.f;
+#pragma unroll
+        for (int c = 0; c < 12; c++) s = fmaxf(s, fmaxf(fabsf(o[c].re), fabsf(o[c].im)));
+        const float sd = s > 0.f ? s : 1.f;
+#pragma unroll
+        for (int c = 0; c < 12; c++) {
+            const float re = s > 0.f ? o[c].re / sd : 0.f, im = s > 0.f ? o[c].im / sd : 0.f;
+            o[c] = {(float)(_Float16)re * s, (float)(_Float16)im * s};
+        }
+    }
+}
+
+constexpr int kCanonRow = 13;  // padded LDS row of one site: 12 complex and one unused
+
+// A block holds 128 checkerboard sites of each parity (waves 0, 1 even, 2, 3 odd): the 256
+// consecutive canonical sites 2 i0 .. 2 i0 + 255, since checkerboard site i of either parity
+// is one of the full sites 2i, 2i + 1.
+template <int SP, int GP, int NE, bool SHX>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HopOcc<SP, 1>::value)))
+dslash_full_kernel(const FullArgs p, const VisitOrder vo) {
+    using R = real_t<SP>;
+    __shared__ __align__(16) Cx<R> buf[256 * kCanonRow];
+    const Geom &g = p.g;
+    const int tid = threadIdx.x;
+    const int par = __builtin_amdgcn_readfirstlane(tid >> 7), l = tid & 127;
+    const int b0 = xcd_tile(blockIdx.x, gridDim.x) * 128;
+    const int n = min(128, g.Vh - b0);
+    const int i0 = visit_order(b0, g, vo);  // (plane blocks are whole tiles: the tile stays contiguous)
+    const int i = i0 + (l < n ? l : n - 1);
+    const SiteXY c = cb_coords(g, i, par);
+    const SiteNbrs nb = site_nbrs(g, i, c);
+    const Spinor fp = par ? p.f[1] : p.f[0];
+    const HopSource a = {par ? p.f[0] : p.f[1], p.gauge};
+    const bool act[1] = {true};
+    Cx<R> acc[1][4][3];
+    hop_sum<SP, GP, 1, NE, false, false, SHX, false, 0>(acc, a, g, par, i, c, nb, 0, act, g.stride, nullptr);
+    // the sums are complete here: the compiler otherwise sinks the arithmetic of all eight
+    // directions into the branch that uses it, keeping every load live (1.3 KB of spills)
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) asm volatile("" : "+v"(acc[0][s][k].re), "+v"(acc[0][s][k].im));
+    const R cH = (R)p.cH;
+    Cx<R> y[12], o[12];
+    load_site<SP, R>(y, fp, g.stride, 0, i);
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) o[s * 3 + k] = cadd(cscale(acc[0][s][k], cH), y[s * 3 + k]);
+    as_stored<SP, R>(o);
+    if (l < n) {
+#pragma unroll
+        for (int k = 0; k < 12; k++) buf[(2 * l + c.b) * kCanonRow + k] = o[k];
+    }
+    __syncthreads();
+    dvec2 *dst = reinterpret_cast<dvec2 *>(p.out) + (size_t)i0 * 24;
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        const int e = k * 256 + tid, site = e / 12;
+        if (site < 2 * n) {
+            const Cx<R> x = buf[site * kCanonRow + (e - site * 12)];
+            dvec2 d;
+            d.x = (double)x.re;
+            d.y = (double)x.im;
+            __builtin_nontemporal_store(d, gptr_w(dst) + e);
+        }
+    }
+}
+
+// Site s of the canonical input as it would read from storage precision SP: components and,
+// for FP16, the site's scale.  half: the spin half a t-hop needs (-1: all; FP16 needs the
+// whole site for its scale).
+template <int SP, typename R>
+__device__ __forceinline__ void load_canon(Cx<R> (&v)[12], R &sc, const double2 *in, size_t s, int half) {
+    const dvec2 *src = reinterpret_cast<const dvec2 *>(in) + s * 12;
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        if (SP == P16 || half < 0 || (k >= 6 * half && k < 6 * half + 6)) {
+            const dvec2 d = gptr(src)[k];
+            v[k] = {(R)d.x, (R)d.y};
+        } else {
+            v[k] = {R(0), R(0)};
+        }
+    }
+    sc = R(1);
+    if constexpr (SP == P16) {
+        float m = 0.f;
+#pragma unroll
+        for (int k = 0; k < 12; k++) m = fmaxf(m, fmaxf(fabsf(v[k].re), fabsf(v[k].im)));
+        const float sd = m > 0.f ? m : 1.f;
+#pragma unroll
+        for (int k = 0; k < 12; k++)
+            v[k] = m > 0.f ? Cx<R>{(float)(_Float16)(v[k].re / sd), (float)(_Float16)(v[k].im / sd)} : Cx<R>{R(0), R(0)};
+        sc = m;
+    }
+}
+
+// Wave 1 + mu of a block: the two hops along MU of the block's 64 output sites.  A neighbour
+// of checkerboard index j is the full site 2j + b', where b' is the output site's b for y, z
+// and t (the coordinate's parity flips with the site's) and 1 - b along x.
+template <int SP, int GP, int NE, int MU>
+__device__ __forceinline__ void small_dir(Cx<real_t<SP>> (&acc)[1][4][3], const FullArgs &p, const HopSource &a,
+                                          const double2 *in, int par, int i, const SiteXY &c, int jf, int jb) {
+    using R = real_t<SP>;
+    const Geom &g = p.g;
+    const bool act[1] = {true};
+    const int bn = MU == 0 ? 1 - c.b : c.b;
+    const R one = R(1);
+    const R sf = MU == 3 && NE == 6 && c.t == g.L[3] - 1 ? -one : one;
+    const R sb = MU == 3 && NE == 6 && c.t == 0 ? -one : one;
+    Cx<R> v[12], H[1][2][3];
+    R sc;
+    load_canon<SP, R>(v, sc, in, 2 * (size_t)jf + bn, MU == 3 ? 1 : -1);
+    proj_in<SP, MU, true, false>(v, sc, H[0]);
+    hop_dir<SP, GP, 1, NE, false, false, MU, true, 1, false, 0>(acc, a, act, 0, jf, par, i, sf, g.stride, H);
+    load_canon<SP, R>(v, sc, in, 2 * (size_t)jb + bn, MU == 3 ? 0 : -1);
+    proj_in<SP, MU, false, false>(v, sc, H[0]);
+    hop_dir<SP, GP, 1, NE, false, false, MU, false, 1, false, 0>(acc, a, act, 0, jb, 1 - par, jb, sb, g.stride, H);
+}
+
+// p.par = 0 or 1: the parity hop alone (out = cH H in on that parity's sites); 2: D on both.
+// blockIdx.x = (tile * parities + parity) * nrhs + rhs.  The four directions are added in
+// the order of the solvers' direction split.
+template <int SP, int GP, int NE>
+__global__ void __launch_bounds__(320) dslash_small_kernel(const FullArgs p) {
+    using R = real_t<SP>;
+    const Geom &g = p.g;
+    const int lb = blockIdx.x, tp = lb / p.nrhs, rhs = lb - tp * p.nrhs;
+    const int par = p.par == 2 ? (tp & 1) : p.par, tile = p.par == 2 ? (tp >> 1) : tp;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+    const int l = tile * 64 + lane;
+    const bool valid = l < g.Vh;
+    const int i = valid ? l : g.Vh - 1;
+    const SiteXY c = cb_coords(g, i, par);
+    const double2 *in = p.in + (size_t)rhs * g.Vh * 24;
+    __shared__ R part[4][24][64];
+    Cx<R> y[12];
+    R ys = R(1);
+    if (wv > 0) {
+        Cx<R> acc[1][4][3];
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int k = 0; k < 3; k++) acc[0][s][k] = {R(0), R(0)};
+        const HopSource a = {Spinor(), p.gauge};
+        const SiteNbrs nb = site_nbrs(g, i, c);
+        if (wv == 1) small_dir<SP, GP, NE, 0>(acc, p, a, in, par, i, c, nb.xp, nb.xm);
+        else if (wv == 2) small_dir<SP, GP, NE, 1>(acc, p, a, in, par, i, c, nb.yp, nb.ym);
+        else if (wv == 3) small_dir<SP, GP, NE, 2>(acc, p, a, in, par, i, c, nb.zp, nb.zm);
+        else small_dir<SP, GP, NE, 3>(acc, p, a, in, par, i, c, nb.tp, nb.tm);
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                part[wv - 1][2 * (s * 3 + k)][lane] = acc[0][s][k].re;
+                part[wv - 1][2 * (s * 3 + k) + 1][lane] = acc[0][s][k].im;
+            }
+    } else if (p.par == 2) {
+        load_canon<SP, R>(y, ys, in, 2 * (size_t)i + c.b, -1);
+        if constexpr (SP == P16) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) y[k] = cscale(y[k], ys);
+        }
+    }
+    __syncthreads();
+    if (wv != 0) return;
+    const R cH = (R)p.cH;
+    Cx<R> o[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        const Cx<R> t = {((part[0][2 * k][lane] + part[1][2 * k][lane]) + part[2][2 * k][lane]) + part[3][2 * k][lane],
+                         ((part[0][2 * k + 1][lane] + part[1][2 * k + 1][lane]) + part[2][2 * k + 1][lane]) +
+                             part[3][2 * k + 1][lane]};
+        o[k] = cscale(t, cH);
+        if (p.par == 2) o[k] = cadd(o[k], y[k]);
+    }
+    as_stored<SP, R>(o);
+    if (!valid) return;
+    dvec2 *dst = reinterpret_cast<dvec2 *>(p.out) + ((size_t)rhs * g.Vh * 2 + 2 * (size_t)i + c.b) * 12;
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        dvec2 d;
+        d.x = (double)o[k].re;
+        d.y = (double)o[k].im;
+        gptr_w(dst)[k] = d;
+    }
+}
+
+template <int SP, int GP>
+static hipError_t full_pg(const FullArgs &p, int zblk, hipStream_t s) {
+    constexpr bool SHX = SP != P64;  // (FP64 spills with the exchange)
+    const dim3 grid((p.g.Vh + 127) / 128), block(256);
+    const VisitOrder vo = make_visit_order(p.g, zblk);
+    if (p.recon == 12) hipLaunchKernelGGL((dslash_full_kernel<SP, GP, 6, SHX>), grid, block, 0, s, p, vo);
+    else hipLaunchKernelGGL((dslash_full_kernel<SP, GP, 9, SHX>), grid, block, 0, s, p, vo);
+    return hipGetLastError();
+}
+template <int SP, int GP>
+static hipError_t small_pg(const FullArgs &p, hipStream_t s) {
+    const dim3 grid((unsigned)((p.g.Vh + 63) / 64 * (p.par == 2 ? 2 : 1) * p.nrhs)), block(320);
+    if (p.recon == 12) hipLaunchKernelGGL((dslash_small_kernel<SP, GP, 6>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((dslash_small_kernel<SP, GP, 9>), grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_dslash_full(const FullArgs &p, hipStream_t s) {
+    const int sp = p.f[0].prec, gp = p.gprec;
+    if ((p.recon != 12 && p.recon != 18) || p.par != 2 || p.nrhs != 1 || p.f[1].prec != sp) return hipErrorInvalidValue;
+    const int zblk = full_zblk(p.g);
+    if (sp == P64 && gp == P64) return full_pg<P64, P64>(p, zblk, s);
+    if (sp == P32 && gp == P32) return full_pg<P32, P32>(p, zblk, s);
+    if (sp == P16 && gp == P16) return full_pg<P16, P16>(p, zblk, s);
+    if (sp == P16 && gp == P32) return full_pg<P16, P32>(p, zblk, s);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_dslash_small(const FullArgs &p, int sp, hipStream_t s) {
+    const int gp = p.gprec;
+    if ((p.recon != 12 && p.recon != 18) || p.nrhs < 1 || p.nrhs > kMaxRhs || p.par < 0 || p.par > 2)
+        return hipErrorInvalidValue;
+    if (sp == P64 && gp == P64) return small_pg<P64, P64>(p, s);
+    if (sp == P32 && gp == P32) return small_pg<P32, P32>(p, s);
+    if (sp == P16 && gp == P16) return small_pg<P16, P16>(p, s);
+    if (sp == P16 && gp == P32) return small_pg<P16, P32>(p, s);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace wl

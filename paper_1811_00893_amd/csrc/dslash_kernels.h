@@ -113,8 +113,8 @@ __device__ __forceinline__ void proj_in(const Cx<real_t<SP>> (&comp)[12], real_t
 // 1 = its projected half spinors given in H.  LL: the link comes from the block's LDS copy
 // `ll` (see stage_links) instead of global memory.
 template <int SP, int GP, int RPT, int NE, bool G5, bool LNT, int MU, bool FWD, int SRC = 0, bool LL = false,
-          int BAR = -1, int LNE = 0>
-__device__ __forceinline__ void hop_dir(Cx<real_t<SP>> (&acc)[RPT][4][3], const HopArgs &a, const bool (&act)[RPT],
+          int BAR = -1, int LNE = 0, typename A>
+__device__ __forceinline__ void hop_dir(Cx<real_t<SP>> (&acc)[RPT][4][3], const A &a, const bool (&act)[RPT],
                                         int r0, int nbr, int link_par, int link_site, real_t<SP> sgn, int stride,
                                         const Cx<real_t<SP>> (*H)[2][3] = nullptr, const char *ll = nullptr) {
     using R = real_t<SP>;
@@ -206,8 +206,8 @@ __device__ __forceinline__ void hop_dir(Cx<real_t<SP>> (&acc)[RPT][4][3], const 
 // One output site i (all RPT right-hand sides of this lane): gather, project, multiply,
 // reconstruct, epilogue, store; the site's reduction terms are added to red[r][*].
 // Input components of site j (all RPT right-hand sides, raw: before gamma5 and FP16 scale).
-template <int SP, int RPT>
-__device__ __forceinline__ void load_raw(Cx<real_t<SP>> (&v)[RPT][12], real_t<SP> (&vs)[RPT], const HopArgs &a,
+template <int SP, int RPT, typename A>
+__device__ __forceinline__ void load_raw(Cx<real_t<SP>> (&v)[RPT][12], real_t<SP> (&vs)[RPT], const A &a,
                                          const bool (&act)[RPT], int r0, int j, int stride) {
     using R = real_t<SP>;
     constexpr int CPE = SpinorPack<SP>::CPE, NEL = SpinorPack<SP>::NEL;
@@ -231,9 +231,9 @@ __device__ __forceinline__ void load_raw(Cx<real_t<SP>> (&v)[RPT][12], real_t<SP
 // own centre C, and the lane of the same wavefront that holds site j as its centre
 // (lane + j - i) hands its result over; where no lane holds j (the neighbour belongs to
 // another wavefront, or the visiting order is not contiguous there) it is loaded.
-template <int SP, int RPT, int MU, bool FWD, bool G5>
+template <int SP, int RPT, int MU, bool FWD, bool G5, typename A>
 __device__ __forceinline__ void lane_nbr(Cx<real_t<SP>> (&H)[RPT][2][3], const Cx<real_t<SP>> (&C)[RPT][12],
-                                         const real_t<SP> (&Cs)[RPT], const HopArgs &a, const bool (&act)[RPT], int r0,
+                                         const real_t<SP> (&Cs)[RPT], const A &a, const bool (&act)[RPT], int r0,
                                          int i, int j, int stride) {
     using R = real_t<SP>;
     const int lane = (int)threadIdx.x & 63;
@@ -404,36 +404,15 @@ __device__ __forceinline__ void stage_links_full(char *ll, const HopArgs &a, int
     __syncthreads();
 }
 
-template <int SP, int GP, int RPT, int NE, bool G5, bool LNT, bool SHX, bool CLV, bool LL = false, int LNE = 0>
-__device__ __forceinline__ void hop_site(const HopArgs &a, int i, bool valid, int r0, const bool (&act)[RPT],
-                                         double (&red)[RPT][3]) {
+// The sum over the eight directions at output site i (coordinates c, neighbours nb), all
+// RPT right-hand sides of this lane.  ll: the tile's links in LDS (LL).
+template <int SP, int GP, int RPT, int NE, bool G5, bool LNT, bool SHX, bool LL, int LNE, typename A>
+__device__ __forceinline__ void hop_sum(Cx<real_t<SP>> (&acc)[RPT][4][3], const A &a, const Geom &g, int par, int i,
+                                        const SiteXY &c, const SiteNbrs &nb, int r0, const bool (&act)[RPT],
+                                        int stride, const char *ll) {
     using R = real_t<SP>;
-    const Geom &g = a.g;
-    const int stride = g.stride;
-    const int par = a.par, opar = 1 - par;
-    const SiteXY c = cb_coords(g, i, par);
-    const SiteNbrs nb = site_nbrs(g, i, c);
+    const int opar = 1 - par;
     const int xp = nb.xp, xm = nb.xm, yp = nb.yp, ym = nb.ym, zp = nb.zp, zm = nb.zm, tp = nb.tp, tm = nb.tm;
-
-    const char *ll = nullptr;
-    if constexpr (LL) {
-        constexpr int NES = LNE == 9 ? 9 : NE;
-        __shared__ __align__(16) char ll_buf[8 * LinkElems<GP, NES>::N * 64 * LinkPack<GP>::EB];
-        const int lsite[8] = {i, xm, i, ym, i, zm, i, tm};
-        if constexpr (LNE == 9) {
-            const float lsgn[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, c.t == g.L[3] - 1 ? -1.f : 1.f, c.t == 0 ? -1.f : 1.f};
-            stage_links_full<GP>(ll_buf, a, par, lsite, lsgn, stride);
-        } else {
-            stage_links<GP, NE>(ll_buf, a, par, lsite, stride);
-        }
-        ll = ll_buf;
-        bool any = false;
-#pragma unroll
-        for (int r = 0; r < RPT; r++) any |= act[r];
-        if (!any) return;  // after the barrier: this wave's RHS group has finished
-    }
-
-    Cx<R> acc[RPT][4][3];
 #pragma unroll
     for (int r = 0; r < RPT; r++)
 #pragma unroll
@@ -469,6 +448,39 @@ __device__ __forceinline__ void hop_site(const HopArgs &a, int i, bool valid, in
     hop_dir<SP, GP, RPT, NE, G5, LNT, 2, false, 0, LL, -1, LNE>(acc, a, act, r0, zm, opar, zm, one, stride, nullptr, ll);
     hop_dir<SP, GP, RPT, NE, G5, LNT, 3, true, 0, LL, -1, LNE>(acc, a, act, r0, tp, par, i, sgn_tf, stride, nullptr, ll);
     hop_dir<SP, GP, RPT, NE, G5, LNT, 3, false, 0, LL, -1, LNE>(acc, a, act, r0, tm, opar, tm, sgn_tb, stride, nullptr, ll);
+}
+
+template <int SP, int GP, int RPT, int NE, bool G5, bool LNT, bool SHX, bool CLV, bool LL = false, int LNE = 0>
+__device__ __forceinline__ void hop_site(const HopArgs &a, int i, bool valid, int r0, const bool (&act)[RPT],
+                                         double (&red)[RPT][3]) {
+    using R = real_t<SP>;
+    const Geom &g = a.g;
+    const int stride = g.stride;
+    const int par = a.par;
+    const SiteXY c = cb_coords(g, i, par);
+    const SiteNbrs nb = site_nbrs(g, i, c);
+    const int xm = nb.xm, ym = nb.ym, zm = nb.zm, tm = nb.tm;
+
+    const char *ll = nullptr;
+    if constexpr (LL) {
+        constexpr int NES = LNE == 9 ? 9 : NE;
+        __shared__ __align__(16) char ll_buf[8 * LinkElems<GP, NES>::N * 64 * LinkPack<GP>::EB];
+        const int lsite[8] = {i, xm, i, ym, i, zm, i, tm};
+        if constexpr (LNE == 9) {
+            const float lsgn[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, c.t == g.L[3] - 1 ? -1.f : 1.f, c.t == 0 ? -1.f : 1.f};
+            stage_links_full<GP>(ll_buf, a, par, lsite, lsgn, stride);
+        } else {
+            stage_links<GP, NE>(ll_buf, a, par, lsite, stride);
+        }
+        ll = ll_buf;
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < RPT; r++) any |= act[r];
+        if (!any) return;  // after the barrier: this wave's RHS group has finished
+    }
+
+    Cx<R> acc[RPT][4][3];
+    hop_sum<SP, GP, RPT, NE, G5, LNT, SHX, LL, LNE>(acc, a, g, par, i, c, nb, r0, act, stride, ll);
 
 #pragma unroll
     for (int r = 0; r < RPT; r++) {

@@ -24,38 +24,129 @@ __device__ __forceinline__ int full_site(const Geom &g, int i, int par, int *t_o
     return x + g.L[0] * (c.y + g.L[1] * (c.z + g.L[2] * c.t));
 }
 
+// Canonical spinors <-> parity planes.  Both directions move every byte once, so they are
+// bound by HBM; a canonical site is 192 contiguous bytes and a plane element 16, so a lane
+// that reads its own site from the canonical side touches 64 lines per load and leaves the
+// gathering of the sectors to the caches (102 us per parity of 32^3 x 64 in FP64, 4.0 TB/s).
+// Here the canonical side is read and written in whole runs and a tile goes through LDS
+// (one padded row of 13 elements per site: the 16-byte accesses of 16 lanes fall into
+// different banks), where each lane picks up its own site.
+//   both parities: checkerboard site i of either parity is one of the full sites 2i, 2i + 1,
+//     so a block takes 128 checkerboard sites of each parity = 256 consecutive sites = 48 KB;
+//   one parity: a wave takes its 64 sites' 192-byte chunks, five and a third of them per
+//     access.
+constexpr int kRow = 13;  // padded LDS row: elements of one site
+
 template <int P>
-__global__ void __launch_bounds__(256) to_parity_kernel(Spinor f, const double2 *canon, Geom g, int par,
-                                                        double scale) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.Vh) return;
-    const int rhs = blockIdx.y;
-    const size_t V = (size_t)g.Vh * 2;
-    const int s = full_site(g, i, par, nullptr);
-    const double2 *src = canon + ((size_t)rhs * V + s) * 12;
+__global__ void __launch_bounds__(256) split_kernel(Spinor fe, Spinor fo, const double2 *canon, Geom g) {
     using R = real_t<P>;
-    Cx<R> v[12];
+    __shared__ __align__(16) Cx<R> buf[256 * kRow];
+    const int tid = threadIdx.x, rhs = blockIdx.y;
+    const int i0 = blockIdx.x * 128;
+    const int n = min(128, g.Vh - i0);  // checkerboard sites of each parity in this tile
+    const dvec2 *src = reinterpret_cast<const dvec2 *>(canon) + ((size_t)rhs * g.Vh + i0) * 24;
 #pragma unroll
     for (int k = 0; k < 12; k++) {
-        const double2 d = src[k];
-        v[k] = {(R)(d.x * scale), (R)(d.y * scale)};
+        const int e = k * 256 + tid, site = e / 12;
+        if (site < 2 * n) {
+            const dvec2 d = __builtin_nontemporal_load(gptr(src) + e);
+            buf[site * kRow + (e - site * 12)] = {(R)d.x, (R)d.y};
+        }
     }
+    __syncthreads();
+    const int par = __builtin_amdgcn_readfirstlane(tid >> 7), l = tid & 127;
+    if (l >= n) return;
+    const SiteXY c = cb_coords(g, i0 + l, par);
+    Cx<R> v[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) v[k] = buf[(2 * l + c.b) * kRow + k];
+    store_site<P, R>(par ? fo : fe, g.stride, rhs, i0 + l, v);
+}
+
+template <int P>
+__global__ void __launch_bounds__(256) join_kernel(double2 *canon, Spinor fe, Spinor fo, Geom g) {
+    using R = real_t<P>;
+    __shared__ __align__(16) Cx<R> buf[256 * kRow];
+    const int tid = threadIdx.x, rhs = blockIdx.y;
+    const int i0 = blockIdx.x * 128;
+    const int n = min(128, g.Vh - i0);
+    const int par = __builtin_amdgcn_readfirstlane(tid >> 7), l = tid & 127;
+    if (l < n) {
+        const SiteXY c = cb_coords(g, i0 + l, par);
+        Cx<R> v[12];
+        load_site<P, R, true>(v, par ? fo : fe, g.stride, rhs, i0 + l);
+#pragma unroll
+        for (int k = 0; k < 12; k++) buf[(2 * l + c.b) * kRow + k] = v[k];
+    }
+    __syncthreads();
+    dvec2 *dst = reinterpret_cast<dvec2 *>(canon) + ((size_t)rhs * g.Vh + i0) * 24;
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        const int e = k * 256 + tid, site = e / 12;
+        if (site < 2 * n) {
+            const Cx<R> x = buf[site * kRow + (e - site * 12)];
+            dvec2 d;
+            d.x = (double)x.re;
+            d.y = (double)x.im;
+            __builtin_nontemporal_store(d, gptr_w(dst) + e);
+        }
+    }
+}
+
+// One parity.  Lane l of a wave owns checkerboard site i0 + l; the wave's chunks are moved
+// element by element (element e of the wave: component e % 12 of its site e / 12).
+template <int P>
+__global__ void __launch_bounds__(256) split_one_kernel(Spinor f, const double2 *canon, Geom g, int par) {
+    using R = real_t<P>;
+    __shared__ __align__(16) Cx<R> buf[256 * kRow];
+    const int i = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63, rhs = blockIdx.y;
+    const bool valid = i < g.Vh;
+    const int s = full_site(g, valid ? i : g.Vh - 1, par, nullptr);  // (past the end: the last site again)
+    const dvec2 *src = reinterpret_cast<const dvec2 *>(canon) + (size_t)rhs * g.Vh * 24;
+    Cx<R> *row = buf + (threadIdx.x & ~63) * kRow;
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        const int e = k * 64 + lane, o = e / 12;
+        const int so = __shfl(s, o, 64);
+        const dvec2 d = __builtin_nontemporal_load(gptr(src) + ((size_t)so * 12 + (e - o * 12)));
+        row[o * kRow + (e - o * 12)] = {(R)d.x, (R)d.y};
+    }
+    __syncthreads();
+    if (!valid) return;
+    Cx<R> v[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) v[k] = row[lane * kRow + k];
     store_site<P, R>(f, g.stride, rhs, i, v);
 }
 
 template <int P>
-__global__ void __launch_bounds__(256) from_parity_kernel(double2 *canon, Spinor f, Geom g, int par) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.Vh) return;
-    const int rhs = blockIdx.y;
-    const size_t V = (size_t)g.Vh * 2;
-    const int s = full_site(g, i, par, nullptr);
+__global__ void __launch_bounds__(256) join_one_kernel(double2 *canon, Spinor f, Geom g, int par) {
     using R = real_t<P>;
-    Cx<R> v[12];
-    load_site<P, R>(v, f, g.stride, rhs, i);
-    double2 *dst = canon + ((size_t)rhs * V + s) * 12;
+    __shared__ __align__(16) Cx<R> buf[256 * kRow];
+    const int i = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63, rhs = blockIdx.y;
+    const bool valid = i < g.Vh;
+    const int s = valid ? full_site(g, i, par, nullptr) : -1;
+    Cx<R> *row = buf + (threadIdx.x & ~63) * kRow;
+    if (valid) {
+        Cx<R> v[12];
+        load_site<P, R, true>(v, f, g.stride, rhs, i);
 #pragma unroll
-    for (int k = 0; k < 12; k++) dst[k] = make_double2((double)v[k].re, (double)v[k].im);
+        for (int k = 0; k < 12; k++) row[lane * kRow + k] = v[k];
+    }
+    __syncthreads();
+    dvec2 *dst = reinterpret_cast<dvec2 *>(canon) + (size_t)rhs * g.Vh * 24;
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        const int e = k * 64 + lane, o = e / 12;
+        const int so = __shfl(s, o, 64);
+        if (so >= 0) {
+            const Cx<R> x = row[o * kRow + (e - o * 12)];
+            dvec2 d;
+            d.x = (double)x.re;
+            d.y = (double)x.im;
+            __builtin_nontemporal_store(d, gptr_w(dst) + ((size_t)so * 12 + (e - o * 12)));
+        }
+    }
 }
 
 template <int PD>
@@ -196,26 +287,51 @@ __global__ void check_finite_kernel(const double *p, size_t n, int *flag) {
 // ---------------------------------------------------------------------------------
 static inline dim3 site_grid(const Geom &g, int ny) { return dim3((g.Vh + 255) / 256, ny); }
 
-hipError_t launch_to_parity(Spinor f, const double *canon, const Geom &g, int par, int nrhs, double scale,
-                            hipStream_t s) {
-    const dim3 grid = site_grid(g, nrhs), block(256);
+hipError_t launch_split(Spinor fe, Spinor fo, const double *canon, const Geom &g, int nrhs, hipStream_t s) {
+    if (fe.prec != fo.prec) return hipErrorInvalidValue;
+    const dim3 grid((g.Vh + 127) / 128, nrhs), block(256);
     const double2 *c = reinterpret_cast<const double2 *>(canon);
-    switch (f.prec) {
-        case P64: hipLaunchKernelGGL(to_parity_kernel<P64>, grid, block, 0, s, f, c, g, par, scale); break;
-        case P32: hipLaunchKernelGGL(to_parity_kernel<P32>, grid, block, 0, s, f, c, g, par, scale); break;
-        case P16: hipLaunchKernelGGL(to_parity_kernel<P16>, grid, block, 0, s, f, c, g, par, scale); break;
+    switch (fe.prec) {
+        case P64: hipLaunchKernelGGL(split_kernel<P64>, grid, block, 0, s, fe, fo, c, g); break;
+        case P32: hipLaunchKernelGGL(split_kernel<P32>, grid, block, 0, s, fe, fo, c, g); break;
+        case P16: hipLaunchKernelGGL(split_kernel<P16>, grid, block, 0, s, fe, fo, c, g); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_from_parity(double *canon, Spinor f, const Geom &g, int par, int nrhs, hipStream_t s) {
+hipError_t launch_split_one(Spinor f, const double *canon, const Geom &g, int par, int nrhs, hipStream_t s) {
+    const dim3 grid = site_grid(g, nrhs), block(256);
+    const double2 *c = reinterpret_cast<const double2 *>(canon);
+    switch (f.prec) {
+        case P64: hipLaunchKernelGGL(split_one_kernel<P64>, grid, block, 0, s, f, c, g, par); break;
+        case P32: hipLaunchKernelGGL(split_one_kernel<P32>, grid, block, 0, s, f, c, g, par); break;
+        case P16: hipLaunchKernelGGL(split_one_kernel<P16>, grid, block, 0, s, f, c, g, par); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_join(double *canon, Spinor fe, Spinor fo, const Geom &g, int nrhs, hipStream_t s) {
+    if (fe.prec != fo.prec) return hipErrorInvalidValue;
+    const dim3 grid((g.Vh + 127) / 128, nrhs), block(256);
+    double2 *c = reinterpret_cast<double2 *>(canon);
+    switch (fe.prec) {
+        case P64: hipLaunchKernelGGL(join_kernel<P64>, grid, block, 0, s, c, fe, fo, g); break;
+        case P32: hipLaunchKernelGGL(join_kernel<P32>, grid, block, 0, s, c, fe, fo, g); break;
+        case P16: hipLaunchKernelGGL(join_kernel<P16>, grid, block, 0, s, c, fe, fo, g); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_join_one(double *canon, Spinor f, const Geom &g, int par, int nrhs, hipStream_t s) {
     const dim3 grid = site_grid(g, nrhs), block(256);
     double2 *c = reinterpret_cast<double2 *>(canon);
     switch (f.prec) {
-        case P64: hipLaunchKernelGGL(from_parity_kernel<P64>, grid, block, 0, s, c, f, g, par); break;
-        case P32: hipLaunchKernelGGL(from_parity_kernel<P32>, grid, block, 0, s, c, f, g, par); break;
-        case P16: hipLaunchKernelGGL(from_parity_kernel<P16>, grid, block, 0, s, c, f, g, par); break;
+        case P64: hipLaunchKernelGGL(join_one_kernel<P64>, grid, block, 0, s, c, f, g, par); break;
+        case P32: hipLaunchKernelGGL(join_one_kernel<P32>, grid, block, 0, s, c, f, g, par); break;
+        case P16: hipLaunchKernelGGL(join_one_kernel<P16>, grid, block, 0, s, c, f, g, par); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

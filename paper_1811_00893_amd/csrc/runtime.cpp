@@ -415,11 +415,7 @@ static LaunchCfg tune_hop(wilson_ctx *ctx, const HopArgs &a, double *best_ms) {
     return best;
 }
 
-int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes) {
-    if (a.nrhs < 1 || a.nrhs > kMaxRhs) throw Error(WILSON_INVALID_ARG, "nrhs out of range");
-    if (a.out.data == a.in.data || (a.has_y && a.out.data == a.y.data) || (a.has_z && a.out.data == a.z.data))
-        throw Error(WILSON_INVALID_ARG, "hop output aliases an input");
-    if (a.clov_mode != CLV_NONE && a.clov == nullptr) throw Error(WILSON_INVALID_ARG, "clover blocks missing");
+bool hop_pinned(wilson_ctx *ctx) {
     if (!ctx->cfg_read) {
         ctx->cfg_read = true;
         const char *fc = std::getenv("WILSON_HOP_CFG");
@@ -429,6 +425,15 @@ int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes) {
                                       &c.wsplit, &c.shx, &c.dsplit, &c.ldsl, &c.tm) >= 4;
         }
     }
+    return ctx->forced;
+}
+
+int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes) {
+    if (a.nrhs < 1 || a.nrhs > kMaxRhs) throw Error(WILSON_INVALID_ARG, "nrhs out of range");
+    if (a.out.data == a.in.data || (a.has_y && a.out.data == a.y.data) || (a.has_z && a.out.data == a.z.data))
+        throw Error(WILSON_INVALID_ARG, "hop output aliases an input");
+    if (a.clov_mode != CLV_NONE && a.clov == nullptr) throw Error(WILSON_INVALID_ARG, "clover blocks missing");
+    hop_pinned(ctx);
     LaunchCfg cfg;
     const wilson_ctx::HotKey hk = {a.in.prec, a.gprec, a.recon, rhs_class(a.nrhs), {a.g.L[0], a.g.L[1], a.g.L[2], a.g.L[3]}};
     const wilson_ctx::HotKey *found = nullptr;

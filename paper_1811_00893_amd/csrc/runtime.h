@@ -143,7 +143,7 @@ struct wilson_ctx {
     };
     std::vector<Pending> pending;
     std::vector<hipEvent_t> event_pool;
-    // pinned hop configuration (WILSON_HOP_CFG), read at the context's first hop launch
+    // pinned hop configuration (WILSON_HOP_CFG), read at the context's first hop
     bool cfg_read = false;
     bool forced = false;
     wl::LaunchCfg forced_cfg;
@@ -180,7 +180,12 @@ struct wilson_ctx {
     wl::PinnedBuf pinned;            // small host mirror
     // cached workspaces: the last dslash shape, and up to 4 solve shapes (LRU)
     std::shared_ptr<void> dslash_ws;
-    std::string dslash_key;
+    struct DslashKey {
+        int L[4], prec, nrhs;
+        bool operator==(const DslashKey &o) const {
+            return L[0] == o.L[0] && L[1] == o.L[1] && L[2] == o.L[2] && L[3] == o.L[3] && prec == o.prec && nrhs == o.nrhs;
+        }
+    } dslash_key = {};
     std::vector<std::pair<std::string, std::shared_ptr<void>>> solve_cache;
     void *stage(wl::DevBuf &b, size_t bytes);
 };
@@ -191,6 +196,8 @@ namespace wl {
 // algorithmic_bytes is the per-launch byte count used for achieved-bandwidth figures.
 // Returns the number of blocks launched (the row length of the partials it wrote).
 int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes);
+// Whether a launch shape is pinned for this context (WILSON_HOP_CFG).
+bool hop_pinned(wilson_ctx *ctx);
 // Launch a BLAS kernel (timed as class BLAS).
 void blas(wilson_ctx *ctx, int op, BlasArgs &a, double algorithmic_bytes);
 // Launch any kernel sequence through `launch` (returning hipError_t), timed as class cls.

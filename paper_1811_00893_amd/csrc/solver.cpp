@@ -738,8 +738,7 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
     std::copy(kappa, kappa + nrhs, C.kappa.begin());
 
     // b -> parity fields; |b|^2
-    WL_HIP(launch_to_parity(C.b_e.f, b_canon, g, 0, nrhs, 1.0, ctx->stream));
-    WL_HIP(launch_to_parity(C.b_o.f, b_canon, g, 1, nrhs, 1.0, ctx->stream));
+    WL_HIP(launch_split(C.b_e.f, C.b_o.f, b_canon, g, nrhs, ctx->stream));
     {
         std::vector<RhsState> h(nrhs);
         std::memset(h.data(), 0, sizeof(RhsState) * nrhs);
@@ -757,7 +756,7 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
         stop2[k] = tol[k] * tol[k] * bn2[k];
     }
     if (prm.use_x0) {
-        WL_HIP(launch_to_parity(C.x_e.f, x_canon, g, 0, nrhs, 1.0, ctx->stream));
+        WL_HIP(launch_split_one(C.x_e.f, x_canon, g, 0, nrhs, ctx->stream));
     } else {
         WL_HIP(launch_zero(C.x_e.f, g, nrhs, ctx->stream));
     }
@@ -1018,8 +1017,7 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
         if (bn2[k] == 0.0) { status[k] = WILSON_OK; res2[k] = 0.0; }
 
     // x -> canonical
-    WL_HIP(launch_from_parity(x_canon, C.x_e.f, g, 0, nrhs, ctx->stream));
-    WL_HIP(launch_from_parity(x_canon, C.x_o.f, g, 1, nrhs, ctx->stream));
+    WL_HIP(launch_join(x_canon, C.x_e.f, C.x_o.f, g, nrhs, ctx->stream));
     WL_HIP(hipStreamSynchronize(ctx->stream));
     ctx->drain_timing();
     const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -1044,55 +1042,103 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
 }
 
 // ---------------------------------------------------------------------------------
+// Parity planes of a Dslash call: the input's (the hops' and the full kernel's operand) and
+// the output's, where the result passes through planes.
 struct DslashWs {
-    FieldBuf in_e, in_o, out_e, out_o;
+    FieldBuf in[2], out[2];
 };
+
+// The small kernel (canonical in and out, one launch) up to this many output sites of a call
+// (parities and right-hand sides counted).  It gathers from array-of-structures memory, so
+// it pays while the input stays in the caches and launches count.  FP64, us, small kernel
+// against conversions and hops: D at 8^4 6.4 / 13, 8^2x16^2 7.4 / 14, 16^4 27 / 28, 16^2x32^2
+// 81 / 79; one parity hop at 16^3x32 25 / 34, at 16^2x32^2 50 / 58.  FP32 and FP16 take it
+// below 4096 sites per parity only, the lattices whose solver hops split the directions over
+// waves without tuning (FP32, 8^4: 6.2 / 12): it adds the directions in that order, and a
+// result at the precision of its storage should not change with the kernel.
+constexpr size_t kSmallSites = (size_t)1 << 17;
+constexpr int kSmallVhLow = 4096;
 
 void dslash_device(wilson_ctx *ctx, const wilson_gauge *G, double *out, const double *in, double kappa, int parity,
                    int precision, int nrhs) {
     const Geom &g = G->g;
     const int P = inner_prec(precision), GP = inner_gauge_prec(precision);
     if (!G->links(GP)) throw Error(WILSON_INVALID_ARG, "gauge field lacks the link precision requested");
-    std::ostringstream os;
-    os << (const void *)G << " " << P << " " << nrhs;
-    std::shared_ptr<DslashWs> ws;
-    if (ctx->dslash_ws && ctx->dslash_key == os.str()) {
-        ws = std::static_pointer_cast<DslashWs>(ctx->dslash_ws);
-    } else {
+    const int np = parity == 2 ? 2 : 1;
+    HopArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.g = g;
+    a.nrhs = nrhs;
+    a.gauge = G->links(P == P64 ? P64 : GP);
+    a.gprec = P == P64 ? P64 : GP;
+    a.recon = G->recon;
+    a.in.prec = P;
+    a.has_y = parity == 2;
+    for (int k = 0; k < nrhs; k++) a.cH[k] = -kappa;
+    // The operator kernels run without a clover term (its epilogue stays with the hops) and
+    // not where a launch shape is pinned (the pinned hop is what such a context asks for).
+    const bool own = !hop_pinned(ctx) && !(parity == 2 && G->has_clover());
+    FullArgs f;
+    std::memset(&f, 0, sizeof f);
+    f.g = g;
+    f.par = parity;
+    f.nrhs = nrhs;
+    f.in = reinterpret_cast<const double2 *>(in);
+    f.out = reinterpret_cast<double2 *>(out);
+    f.gauge = a.gauge;
+    f.gprec = a.gprec;
+    f.recon = a.recon;
+    f.cH = -kappa;
+    auto run_full = [&](auto &&launch) {
+        ctx->hop_launch_count++;
+        ctx->flops_issued += 1320.0 * g.Vh * nrhs * np;
+        timed_launch(ctx, WILSON_KERNEL_HOP, np * hop_bytes(a), launch);
+    };
+    // planes for every form of the call, made at a shape's first call (a later one may be captured)
+    const wilson_ctx::DslashKey key = {{G->dims[0], G->dims[1], G->dims[2], G->dims[3]}, P, nrhs};
+    if (!ctx->dslash_ws || !(ctx->dslash_key == key)) {
         ctx->dslash_ws.reset();
         WL_HIP(hipStreamSynchronize(ctx->stream));
-        ws = std::make_shared<DslashWs>();
-        ws->in_e.make(P, g, nrhs); ws->in_o.make(P, g, nrhs);
-        ws->out_e.make(P, g, nrhs); ws->out_o.make(P, g, nrhs);
-        ctx->dslash_ws = ws;
-        ctx->dslash_key = os.str();
+        auto made = std::make_shared<DslashWs>();
+        for (FieldBuf *b : {&made->in[0], &made->in[1], &made->out[0], &made->out[1]}) b->make(P, g, nrhs);
+        ctx->dslash_ws = made;
+        ctx->dslash_key = key;
     }
-    WL_HIP(launch_to_parity(ws->in_e.f, in, g, 0, nrhs, 1.0, ctx->stream));
-    WL_HIP(launch_to_parity(ws->in_o.f, in, g, 1, nrhs, 1.0, ctx->stream));
+    DslashWs *ws = static_cast<DslashWs *>(ctx->dslash_ws.get());
+    // The small kernel reads the input while others of its blocks write: only the same array
+    // (a parity hop in place reads one parity and writes the other) or disjoint ones.
+    const size_t n = (size_t)g.Vh * 48 * nrhs;
+    const bool apart = out == in || out + n <= in || in + n <= out;
+    const bool small = (size_t)g.Vh * np * nrhs <= kSmallSites && (P == P64 || g.Vh < kSmallVhLow);
+    if (own && small && apart) {
+        run_full([&]() { return launch_dslash_small(f, P, ctx->stream); });
+        return;
+    }
+    if (own && parity == 2 && nrhs == 1) {
+        f.f[0] = ws->in[0].f;
+        f.f[1] = ws->in[1].f;
+        WL_HIP(launch_split(f.f[0], f.f[1], in, g, nrhs, ctx->stream));
+        run_full([&]() { return launch_dslash_full(f, ctx->stream); });
+        return;
+    }
+    if (parity == 2) WL_HIP(launch_split(ws->in[0].f, ws->in[1].f, in, g, nrhs, ctx->stream));
+    else WL_HIP(launch_split_one(ws->in[1 - parity].f, in, g, 1 - parity, nrhs, ctx->stream));
     for (int par = 0; par < 2; par++) {
         if (parity != 2 && parity != par) continue;
-        HopArgs a;
-        std::memset(&a, 0, sizeof a);
-        a.g = g;
         a.par = par;
-        a.nrhs = nrhs;
-        a.out = par ? ws->out_o.f : ws->out_e.f;
-        a.in = par ? ws->in_e.f : ws->in_o.f;
-        a.gauge = G->links(P == P64 ? P64 : GP);
-        a.gprec = P == P64 ? P64 : GP;
-        a.recon = G->recon;
-        for (int k = 0; k < nrhs; k++) a.cH[k] = -kappa;
+        a.out = ws->out[par].f;
+        a.in = ws->in[1 - par].f;
         if (parity == 2) {  // D psi = T psi - k H psi (T = 1 without a clover term)
-            a.has_y = 1;
-            a.y = par ? ws->in_o.f : ws->in_e.f;
+            a.y = ws->in[par].f;
             if (G->has_clover()) {
                 a.clov = G->clover(false, P, par);
                 a.clov_mode = CLV_Y;
             }
         }
         hop(ctx, a, hop_bytes(a));
-        WL_HIP(launch_from_parity(out, a.out, g, par, nrhs, ctx->stream));
     }
+    if (parity == 2) WL_HIP(launch_join(out, ws->out[0].f, ws->out[1].f, g, nrhs, ctx->stream));
+    else WL_HIP(launch_join_one(out, ws->out[parity].f, g, parity, nrhs, ctx->stream));
 }
 
 // ---------------------------------------------------------------------------------
@@ -1226,8 +1272,7 @@ class BatchEngine {
         s.t0 = std::chrono::steady_clock::now();
         C->kappa[k] = kappa;
         C->select(k, 1);
-        WL_HIP(launch_to_parity(C->V(C->b_e.f), b_dev, C->g, 0, 1, 1.0, ctx->stream));
-        WL_HIP(launch_to_parity(C->V(C->b_o.f), b_dev, C->g, 1, 1, 1.0, ctx->stream));
+        WL_HIP(launch_split(C->V(C->b_e.f), C->V(C->b_o.f), b_dev, C->g, 1, ctx->stream));
         C->norm2_full(C->b_e.f, C->b_o.f, C->sout());
         s.bn2 = C->read_states(C->sout())[0].aux;
         C->select_all();
@@ -1329,8 +1374,7 @@ class BatchEngine {
         Slot &s = slots[k];
         if (s.state != FINISHED) return WILSON_BUSY;
         C->select(k, 1);
-        WL_HIP(launch_from_parity(x_dev, C->V(C->x_e.f), C->g, 0, 1, ctx->stream));
-        WL_HIP(launch_from_parity(x_dev, C->V(C->x_o.f), C->g, 1, 1, ctx->stream));
+        WL_HIP(launch_join(x_dev, C->V(C->x_e.f), C->V(C->x_o.f), C->g, 1, ctx->stream));
         C->select_all();
         if (info) {
             info->iterations = s.iters;
