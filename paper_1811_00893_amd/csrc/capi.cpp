@@ -95,6 +95,45 @@ wilson_ctx *default_ctx() {
     return g_default_ctx;
 }
 
+// Packs canonical links into G (dims and geometry set), reusing its buffers where they fit.
+// recon 12 asks for two-row storage, which needs exact SU(3) links (to well below the FP64
+// parity tolerance): the pack checks them on the way, and anything else is packed again in
+// full.  recon 18 keeps every link in full and checks nothing.
+void pack_gauge(wilson_ctx *ctx, wilson_gauge *G, const double *U, uint32_t precisions, int recon) {
+    const size_t links = (size_t)72 * G->dims[0] * G->dims[1] * G->dims[2] * G->dims[3];  // doubles
+    DevBuf tmp;
+    Staged su(ctx, tmp, U, links * sizeof(double), true);
+    auto pack = [&](int rc, int *flag) {
+        void *dst[3];
+        for (int prec = 0; prec < 3; prec++) {
+            const bool want = prec == P64 || (prec == P32 && (precisions & WILSON_GAUGE_FP32)) ||
+                              (prec == P16 && (precisions & WILSON_GAUGE_FP16));
+            const size_t need = gauge_bytes(prec, rc, G->g);
+            if (want && G->U[prec].size() < need) G->U[prec].alloc(need);
+            dst[prec] = want ? G->U[prec].get() : nullptr;
+        }
+        WL_HIP(launch_gauge_pack(dst, su.dev, G->g, rc, 1e-13, flag, ctx->stream));
+        G->recon = rc;
+    };
+    if (recon == 12) {
+        // (the flag is host-mapped: nothing is copied to clear or to read it)
+        if (ctx->pinned.size() < sizeof(int)) ctx->pinned.alloc(256);
+        volatile int *bad = static_cast<volatile int *>(ctx->pinned.host());
+        *bad = 0;
+        pack(12, static_cast<int *>(ctx->pinned.dev()));
+        WL_HIP(hipStreamSynchronize(ctx->stream));
+        if (*bad) recon = 18;
+    }
+    if (recon == 18) pack(18, nullptr);
+    WL_HIP(hipStreamSynchronize(ctx->stream));
+}
+
+// WILSON_RECON=18 forces full storage.
+int wanted_recon() {
+    const char *env = std::getenv("WILSON_RECON");
+    return env && std::strcmp(env, "18") == 0 ? 18 : 12;
+}
+
 wilson_gauge *load_gauge(wilson_ctx *ctx, const double *U, const int32_t *dims, uint32_t precisions) {
     check_dims(dims);
     WL_CHECK_ARG(U != nullptr, "U is NULL");
@@ -102,39 +141,70 @@ wilson_gauge *load_gauge(wilson_ctx *ctx, const double *U, const int32_t *dims, 
     try {
         G->g = make_geom(dims);
         std::memcpy(G->dims, dims, sizeof G->dims);
-        const size_t links = (size_t)72 * dims[0] * dims[1] * dims[2] * dims[3];  // doubles
-        DevBuf tmp;
-        Staged su(ctx, tmp, U, links * sizeof(double), true);
-        // Two-row storage needs exact SU(3) links (to well below the FP64 parity tolerance);
-        // anything else is kept in full.  WILSON_RECON=18 forces full storage.
-        int recon = 12;
-        const char *env = std::getenv("WILSON_RECON");
-        if (env && std::strcmp(env, "18") == 0) recon = 18;
-        if (recon == 12) {
-            if (ctx->flag.size() < sizeof(int)) ctx->flag.alloc(256);
-            static const int zero = 0;
-            WL_HIP(hipMemcpyAsync(ctx->flag.get(), &zero, sizeof(int), hipMemcpyHostToDevice, ctx->stream));
-            WL_HIP(launch_su3_check(su.dev, links / 18, 1e-13, ctx->flag.as<int>(), ctx->stream));
-            int bad = 0;
-            WL_HIP(hipMemcpyAsync(&bad, ctx->flag.get(), sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-            WL_HIP(hipStreamSynchronize(ctx->stream));
-            if (bad) recon = 18;
-        }
-        G->recon = recon;
-        for (int prec = 0; prec < 3; prec++) {
-            const bool want = prec == P64 || (prec == P32 && (precisions & WILSON_GAUGE_FP32)) ||
-                              (prec == P16 && (precisions & WILSON_GAUGE_FP16));
-            if (!want) continue;
-            G->U[prec].alloc(gauge_bytes(prec, recon, G->g));
-            WL_HIP(launch_gauge_pack(G->U[prec].get(), prec, su.dev, G->g, recon, ctx->stream));
-        }
-        WL_HIP(hipStreamSynchronize(ctx->stream));
+        pack_gauge(ctx, G, U, precisions, wanted_recon());
     } catch (...) {
         delete G;
         throw;
     }
     return G;
 }
+
+// The plain entry points take the links with every call.  Their packed links live in one
+// field kept with the default context (guarded by g_default_mu, like that context), so that a
+// program calling them in a loop does not allocate and free device memory each time: the
+// links are packed anew by every call, only the buffers stay.  Another shape or device
+// replaces them, a field of more than kPlainKeep bytes is released when its call ends, and
+// they are given back when an allocation of the library fails.
+constexpr size_t kPlainKeep = size_t(512) << 20;
+wilson_gauge *g_plain = nullptr;
+int g_plain_device = 0;
+thread_local bool tl_in_plain = false;
+
+// the field and the Dslash planes of its shape (g_default_mu held)
+void drop_plain() {
+    if (g_default_ctx) g_default_ctx->dslash_ws.reset();
+    delete g_plain;
+    g_plain = nullptr;
+}
+
+bool reclaim_plain() {
+    if (tl_in_plain) return false;
+    std::unique_lock<std::mutex> lk(g_default_mu, std::try_to_lock);
+    if (!lk.owns_lock() || !g_plain) return false;
+    drop_plain();
+    return true;
+}
+
+struct PlainGauge {
+    wilson_gauge *G = nullptr;
+    PlainGauge(wilson_ctx *ctx, const double *U, const int32_t *dims, int recon) {
+        int dev = 0;
+        WL_HIP(hipGetDevice(&dev));
+        tl_in_plain = true;
+        try {
+            if (g_plain && (g_plain_device != dev || std::memcmp(g_plain->dims, dims, sizeof g_plain->dims) != 0))
+                drop_plain();
+            if (!g_plain) {
+                std::unique_ptr<wilson_gauge> made(new wilson_gauge());
+                made->g = make_geom(dims);
+                std::memcpy(made->dims, dims, sizeof made->dims);
+                g_plain = made.release();
+                g_plain_device = dev;
+                set_reclaim(reclaim_plain);
+            }
+            pack_gauge(ctx, g_plain, U, 0, recon);
+        } catch (...) {
+            end(true);
+            throw;
+        }
+        G = g_plain;
+    }
+    ~PlainGauge() { end(G->bytes() > kPlainKeep || std::uncaught_exceptions() > 0); }
+    static void end(bool drop) {
+        if (drop) drop_plain();
+        tl_in_plain = false;
+    }
+};
 
 int report(const Error &e) {
     set_last_error(e.what());
@@ -352,21 +422,14 @@ int wilson_dslash(double *out, const double *in, const double *U, double kappa, 
     WL_CHECK_ARG(std::isfinite(kappa), "kappa must be finite");
     wilson_ctx *ctx = default_ctx();
     std::lock_guard<std::mutex> lk(g_default_mu);
-    wilson_gauge *G = load_gauge(ctx, U, dims, 0);
-    try {
-        const size_t bytes = spinor_doubles(dims, 1) * sizeof(double);
-        Staged si(ctx, ctx->stage_in, in, bytes, true);
-        Staged so(ctx, ctx->stage_out, out, bytes, parity != 2);
-        dslash_device(ctx, G, so.dev, si.dev, kappa, parity, WILSON_FP64, 1);
-        so.copy_out();
-        WL_HIP(hipStreamSynchronize(ctx->stream));
-    } catch (...) {
-        ctx->dslash_ws.reset();
-        delete G;
-        throw;
-    }
-    ctx->dslash_ws.reset();
-    delete G;
+    // one application: packing two rows would save less than the SU(3) check costs
+    PlainGauge plain(ctx, U, dims, 18);
+    const size_t bytes = spinor_doubles(dims, 1) * sizeof(double);
+    Staged si(ctx, ctx->stage_in, in, bytes, true);
+    Staged so(ctx, ctx->stage_out, out, bytes, parity != 2);
+    dslash_device(ctx, plain.G, so.dev, si.dev, kappa, parity, WILSON_FP64, 1);
+    so.copy_out();
+    WL_HIP(hipStreamSynchronize(ctx->stream));
     return WILSON_OK;
     API_END
 }
@@ -443,22 +506,15 @@ int wilson_solve(double *x, const double *b, const double *U, double kappa, cons
     check_solve_args(&kappa, &tol, 1, nullptr);
     wilson_ctx *ctx = default_ctx();
     std::lock_guard<std::mutex> lk(g_default_mu);
-    wilson_gauge *G = load_gauge(ctx, U, dims, 0);
-    int st;
-    try {
-        SolveParams p;
-        p.maxiter = maxiter;
-        const size_t bytes = spinor_doubles(dims, 1) * sizeof(double);
-        Staged sb(ctx, ctx->stage_in, b, bytes, true);
-        Staged sx(ctx, ctx->stage_out, x, bytes, false);
-        st = solve_device(ctx, G, sx.dev, sb.dev, 1, &kappa, &tol, p, nullptr);
-        sx.copy_out();
-        WL_HIP(hipStreamSynchronize(ctx->stream));
-    } catch (...) {
-        delete G;
-        throw;
-    }
-    delete G;
+    PlainGauge plain(ctx, U, dims, wanted_recon());
+    SolveParams p;
+    p.maxiter = maxiter;
+    const size_t bytes = spinor_doubles(dims, 1) * sizeof(double);
+    Staged sb(ctx, ctx->stage_in, b, bytes, true);
+    Staged sx(ctx, ctx->stage_out, x, bytes, false);
+    const int st = solve_device(ctx, plain.G, sx.dev, sb.dev, 1, &kappa, &tol, p, nullptr);
+    sx.copy_out();
+    WL_HIP(hipStreamSynchronize(ctx->stream));
     return st;
     API_END
 }

@@ -302,9 +302,13 @@ hipError_t launch_convert(Spinor dst, Spinor src, const Geom &g, int nrhs, const
 // x64 += c[rhs] * e (any precision): c = sqrt(state[rhs].aux) with sqrt_aux, else 1.
 hipError_t launch_axpy_f64(Spinor x64, Spinor e, const Geom &g, int nrhs, const RhsState *state, int sqrt_aux,
                            hipStream_t s);
-// Gauge: canonical complex128 links -> parity-split planes in precision prec.
+// Gauge: canonical complex128 links -> parity-split planes, in every precision with a
+// destination in dst (indexed by Prec).
 // recon 18: all 9 entries, t-boundary sign folded in; recon 12: rows 0 and 1 only, no sign.
-hipError_t launch_gauge_pack(void *dst, int prec, const double *canon, const Geom &g, int recon, hipStream_t s);
+// flag (optional, device or host-mapped int): set to 1 if a link is off SU(3) by more than tol
+// (max |U U^dag - 1|, |det U - 1|).
+hipError_t launch_gauge_pack(void *const dst[3], const double *canon, const Geom &g, int recon, double tol, int *flag,
+                             hipStream_t s);
 // Sets *flag (device int) to 1 if any canonical link deviates from SU(3) by more than tol
 // (max |U U^dag - 1|, |det U - 1|).
 hipError_t launch_su3_check(const double *canon, size_t nlinks, double tol, int *flag, hipStream_t s);

@@ -193,51 +193,98 @@ __global__ void __launch_bounds__(256) axpy_f64_kernel(Spinor x, Spinor e, Geom 
     store_site<P64, double>(x, g.stride, rhs, i, xv);
 }
 
+// Largest deviation of one link from SU(3): max over entries of |U U^dag - 1| and |det U - 1|.
+__device__ __forceinline__ double su3_deviation(const Cx<double> (&u)[3][3]) {
+    double dev = 0.0;
+    for (int a = 0; a < 3; a++)
+        for (int b = 0; b < 3; b++) {
+            Cx<double> acc = {a == b ? -1.0 : 0.0, 0.0};
+            for (int k = 0; k < 3; k++) acc = cfma_conj(acc, u[b][k], u[a][k]);  // (U U^dag)_ab - d_ab
+            dev = fmax(dev, fabs(acc.re) + fabs(acc.im));
+        }
+    // det via the first row and the cofactors of rows 1, 2
+    const Cx<double> c0 = csub(cmul(u[1][1], u[2][2]), cmul(u[1][2], u[2][1]));
+    const Cx<double> c1 = csub(cmul(u[1][2], u[2][0]), cmul(u[1][0], u[2][2]));
+    const Cx<double> c2 = csub(cmul(u[1][0], u[2][1]), cmul(u[1][1], u[2][0]));
+    const Cx<double> det = cadd(cadd(cmul(u[0][0], c0), cmul(u[0][1], c1)), cmul(u[0][2], c2));
+    return fmax(dev, fabs(det.re - 1.0) + fabs(det.im));
+}
+
+// Canonical links -> parity-split planes in up to three precisions, with the SU(3) check
+// (CHECK) on the way: one pass over the links (576 B a site, the largest input of the
+// library) where the check and each precision had a pass of its own, and those packed with
+// lanes 1152 B apart on the canonical side.  A block takes 32 checkerboard sites of each
+// parity = 64 consecutive sites = 36 KB through LDS (rows padded by one element) and writes
+// runs of 32 elements of each plane.
+constexpr int kPackSites = 32;
+constexpr int kPackRow = 37;
+
 template <int P>
-__global__ void __launch_bounds__(256) gauge_pack_kernel(void *dst, const double2 *canon, Geom g, int recon) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.Vh) return;
-    const int par = blockIdx.y >> 2, mu = blockIdx.y & 3;
-    int t;
-    const int s = full_site(g, i, par, &t);
-    const int ne = recon == 12 ? 6 : 9;
-    const int nl = link_elems(P, ne);
+__device__ __forceinline__ void pack_planes(void *dst, const double2 *buf, const unsigned char *info, const Geom &g,
+                                            int i0, int n, int recon) {
     constexpr int CPL = LinkPack<P>::CPL;
-    const double sgn = (recon == 18 && mu == 3 && t == g.L[3] - 1) ? -1.0 : 1.0;
-    const double2 *src = canon + ((size_t)s * 4 + mu) * 9;
     using R = real_t<P>;
-    const unsigned off = (unsigned)i * LinkPack<P>::EB;
-    for (int e = 0; e < nl; e++) {
+    const int ne = recon == 12 ? 6 : 9, nl = link_elems(P, ne);
+    for (int it = threadIdx.x; it < 8 * nl * kPackSites; it += 256) {
+        const int c = it % kPackSites, q = it / kPackSites;  // q: plane (par * 4 + mu) * nl + e
+        if (c >= n) continue;
+        const int pm = q / nl, e = q - pm * nl, par = pm >> 2, mu = pm & 3;
+        const double sgn = (recon == 18 && mu == 3 && (info[c] & 2)) ? -1.0 : 1.0;
+        const double2 *src = buf + (2 * c + ((info[c] & 1) ^ par)) * kPackRow + mu * 9;
         Cx<R> x[CPL];
+#pragma unroll
         for (int k = 0; k < CPL; k++) {
             const int idx = e * CPL + k;  // entries past the last are padding
             const double2 d = idx < ne ? src[idx] : make_double2(0.0, 0.0);
             x[k] = {(R)(sgn * d.x), (R)(sgn * d.y)};
         }
-        st_link_elem<P, R>(const_cast<gchar *>(lplane<P>(dst, (par * 4 + mu) * nl + e, g.stride)), off, x);
+        gchar *base = (gchar *)dst + ((size_t)q * g.stride + i0) * LinkPack<P>::EB;
+        st_link_elem<P, R>(base, (unsigned)c * LinkPack<P>::EB, x);
     }
 }
 
-// max over entries of |U U^dag - 1| and |det U - 1| for each link; flag if above tol
+template <bool CHECK>
+__global__ void __launch_bounds__(256) gauge_pack_kernel(void *d64, void *d32, void *d16, const double2 *canon, Geom g,
+                                                         int recon, double tol, int *flag) {
+    __shared__ __align__(16) double2 buf[2 * kPackSites * kPackRow];
+    __shared__ unsigned char info[kPackSites];  // bit 0: x of the even-parity site is odd; bit 1: t = Lt - 1
+    const int tid = threadIdx.x, i0 = blockIdx.x * kPackSites;
+    const int n = min(kPackSites, g.Vh - i0);
+    const dvec2 *src = reinterpret_cast<const dvec2 *>(canon) + (size_t)i0 * 72;
+#pragma unroll
+    for (int k = 0; k < 9; k++) {
+        const int e = k * 256 + tid, site = e / 36;
+        if (site < 2 * n) {
+            const dvec2 d = __builtin_nontemporal_load(gptr(src) + e);
+            buf[site * kPackRow + (e - site * 36)] = make_double2(d.x, d.y);
+        }
+    }
+    if (tid < n) {
+        const SiteXY c = cb_coords(g, i0 + tid, 0);
+        info[tid] = (unsigned char)(c.b | (c.t == g.L[3] - 1 ? 2 : 0));
+    }
+    __syncthreads();
+    if constexpr (CHECK) {
+        if ((tid >> 2) < 2 * n) {
+            const double2 *l = buf + (tid >> 2) * kPackRow + (tid & 3) * 9;
+            Cx<double> u[3][3];
+#pragma unroll
+            for (int e = 0; e < 9; e++) u[e / 3][e % 3] = {l[e].x, l[e].y};
+            if (!(su3_deviation(u) <= tol)) *flag = 1;  // (host-mapped; every writer stores the same word)
+        }
+    }
+    if (d64) pack_planes<P64>(d64, buf, info, g, i0, n, recon);
+    if (d32) pack_planes<P32>(d32, buf, info, g, i0, n, recon);
+    if (d16) pack_planes<P16>(d16, buf, info, g, i0, n, recon);
+}
+
+// flags any link off SU(3) by more than tol
 __global__ void su3_check_kernel(const double2 *canon, size_t nlinks, double tol, int *flag) {
     bool bad = false;
     for (size_t l = blockIdx.x * (size_t)blockDim.x + threadIdx.x; l < nlinks; l += (size_t)gridDim.x * blockDim.x) {
         Cx<double> u[3][3];
         for (int e = 0; e < 9; e++) u[e / 3][e % 3] = {canon[l * 9 + e].x, canon[l * 9 + e].y};
-        double dev = 0.0;
-        for (int a = 0; a < 3; a++)
-            for (int b = 0; b < 3; b++) {
-                Cx<double> acc = {a == b ? -1.0 : 0.0, 0.0};
-                for (int k = 0; k < 3; k++) acc = cfma_conj(acc, u[b][k], u[a][k]);  // (U U^dag)_ab - d_ab
-                dev = fmax(dev, fabs(acc.re) + fabs(acc.im));
-            }
-        // det via the first row and the cofactors of rows 1, 2
-        const Cx<double> c0 = csub(cmul(u[1][1], u[2][2]), cmul(u[1][2], u[2][1]));
-        const Cx<double> c1 = csub(cmul(u[1][2], u[2][0]), cmul(u[1][0], u[2][2]));
-        const Cx<double> c2 = csub(cmul(u[1][0], u[2][1]), cmul(u[1][1], u[2][0]));
-        const Cx<double> det = cadd(cadd(cmul(u[0][0], c0), cmul(u[0][1], c1)), cmul(u[0][2], c2));
-        dev = fmax(dev, fabs(det.re - 1.0) + fabs(det.im));
-        bad |= !(dev <= tol);
+        bad |= !(su3_deviation(u) <= tol);
     }
     if (bad) atomicOr(flag, 1);
 }
@@ -363,16 +410,13 @@ hipError_t launch_axpy_f64(Spinor x64, Spinor e, const Geom &g, int nrhs, const 
     return hipGetLastError();
 }
 
-hipError_t launch_gauge_pack(void *dst, int prec, const double *canon, const Geom &g, int recon, hipStream_t s) {
-    if (recon != 12 && recon != 18) return hipErrorInvalidValue;
-    const dim3 grid = site_grid(g, 8), block(256);
+hipError_t launch_gauge_pack(void *const dst[3], const double *canon, const Geom &g, int recon, double tol, int *flag,
+                             hipStream_t s) {
+    if ((recon != 12 && recon != 18) || (!dst[P64] && !dst[P32] && !dst[P16])) return hipErrorInvalidValue;
+    const dim3 grid((g.Vh + kPackSites - 1) / kPackSites), block(256);
     const double2 *c = reinterpret_cast<const double2 *>(canon);
-    switch (prec) {
-        case P64: hipLaunchKernelGGL(gauge_pack_kernel<P64>, grid, block, 0, s, dst, c, g, recon); break;
-        case P32: hipLaunchKernelGGL(gauge_pack_kernel<P32>, grid, block, 0, s, dst, c, g, recon); break;
-        case P16: hipLaunchKernelGGL(gauge_pack_kernel<P16>, grid, block, 0, s, dst, c, g, recon); break;
-        default: return hipErrorInvalidValue;
-    }
+    if (flag) hipLaunchKernelGGL(gauge_pack_kernel<true>, grid, block, 0, s, dst[P64], dst[P32], dst[P16], c, g, recon, tol, flag);
+    else hipLaunchKernelGGL(gauge_pack_kernel<false>, grid, block, 0, s, dst[P64], dst[P32], dst[P16], c, g, recon, tol, flag);
     return hipGetLastError();
 }
 

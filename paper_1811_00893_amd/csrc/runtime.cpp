@@ -3,6 +3,7 @@
 #include "runtime.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -44,10 +45,20 @@ Geom make_geom(const int32_t dims[4]) {
     return g;
 }
 
+static std::atomic<bool (*)()> g_reclaim{nullptr};
+void set_reclaim(bool (*f)()) { g_reclaim = f; }
+
 void DevBuf::alloc(size_t bytes) {
     release();
     if (bytes == 0) return;
     hipError_t e = hipMalloc(&p_, bytes);
+    if (e == hipErrorOutOfMemory) {
+        bool (*f)() = g_reclaim;
+        if (f && f()) {
+            (void)hipGetLastError();
+            e = hipMalloc(&p_, bytes);
+        }
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         p_ = nullptr;

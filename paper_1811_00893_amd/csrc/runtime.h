@@ -59,6 +59,10 @@ class DevBuf {
     size_t n_ = 0;
 };
 
+// Called when a device allocation runs out of memory: releases what the library keeps between
+// calls without needing it; true if something was released (the allocation is tried again).
+void set_reclaim(bool (*f)());
+
 // Owning pinned host allocation, mapped into the device address space.
 class PinnedBuf {
    public:

@@ -84,3 +84,19 @@ def test_overlapping_arrays(L, dims):
     finally:
         L.wilson_gauge_free(ctx, g)
         L.wilson_context_destroy(ctx)
+
+
+def test_plain_calls_in_turn(L):
+    """The two-call form with links, shapes and storage changing from call to call: the
+    buffers it keeps between calls never carry one call's links into the next."""
+    shapes = [(4, 4, 4, 6), (6, 4, 10, 6), (4, 4, 4, 6), (10, 8, 10, 20)]
+    for n, dims in enumerate(shapes):
+        for scale in (1.0, 1.25, 1.0):  # 1.25 U is not SU(3)
+            U = scale * inputs.gauge_field(dims, eps=0.3, seed=4200 + n)
+            psi = inputs.gaussian_source(dims, seed=4210 + n)
+            out = torch.zeros_like(psi, device=DEV)
+            assert L.wilson_dslash(out, psi.to(DEV), U.to(DEV), 0.11, dims, 2) == 0
+            assert rel(out.cpu().numpy(), oracle.apply_D(psi.numpy(), U.numpy(), 0.11, dims)) < 1e-12
+        x = torch.zeros_like(psi, device=DEV)
+        assert L.wilson_solve(x, psi.to(DEV), U.to(DEV), 0.11, dims, 1e-10, 1000) == 0
+        assert rel(oracle.apply_D(x.cpu().numpy(), U.numpy(), 0.11, dims), psi.numpy()) < 1e-10
