@@ -79,7 +79,7 @@ inline size_t spinor_field_bytes(int prec, const Geom &g) {
 // Per-right-hand-side Krylov state, resident on the device.  The scalars of the
 // iteration are computed on the device, so the host never has to wait for them.
 enum Phase : int { PH_IDLE = 1, PH_RUN = 2, PH_SCONV = 4, PH_DONE = 8, PH_FAIL = 16 };
-enum FailCode : int { FAIL_NONE = 0, FAIL_BREAKDOWN = 1, FAIL_NONFINITE = 2 };
+enum FailCode : int { FAIL_NONE = 0, FAIL_BREAKDOWN = 1, FAIL_NONFINITE = 2, FAIL_DEVICE = 3 };
 
 constexpr int kStateRing = 4;  // host-mapped state mirrors of a solve in flight
 
@@ -288,6 +288,27 @@ hipError_t launch_blas(int op, const BlasArgs &a, hipStream_t s);
 hipError_t launch_finalize(int op, const double *partials, int nvals, int nblocks, int nrhs, RhsState *state,
                            int run_mask, hipStream_t s, RhsState *mirror = nullptr);
 hipError_t launch_zero(const Spinor &f, const Geom &g, int nrhs, hipStream_t s);
+
+// BiCGStab iterations on M_ee in one cooperative launch (small lattices, no clover term): one
+// block per 64-site tile and right-hand side.  Fields hold nrhs right-hand sides; r, rhat and x
+// are set, p and v count as zero with `first`.  scratch: scratch_stride bytes per right-hand
+// side, the first 256 zero at the launch (barrier counter); state: phases, stop2 and scalars.
+struct SmallArgs {
+    Geom g;
+    int nrhs, tiles;
+    int iters;           // at most this many iterations
+    int first;
+    const void *gauge;
+    Spinor r, rh, p, v, s, x, tmp;
+    char *scratch;
+    size_t scratch_stride;
+    RhsState *state;
+    double cH[kMaxRhs];  // -kappa^2
+};
+size_t small_scratch_bytes(const Geom &g, int prec);
+// blocks of the kernel the device holds at once (0: not available)
+int small_max_blocks(int prec, int recon);
+hipError_t launch_bicg_small(const SmallArgs &p, int prec, int recon, hipStream_t s);
 
 // Layout / precision conversion.
 // canonical complex128 [rhs][V][4][3]  <->  parity fields of precision f.prec: both parities

@@ -110,19 +110,23 @@ __device__ __forceinline__ void proj_in(const Cx<real_t<SP>> (&comp)[12], real_t
 }
 
 // SRC selects where the neighbour comes from: 0 = loaded here from the input field;
-// 1 = its projected half spinors given in H.  LL: the link comes from the block's LDS copy
+// 1 = its projected half spinors given in H; 2 = the same and the link's nine entries given.  LL: the link comes from the block's LDS copy
 // `ll` (see stage_links) instead of global memory.
 template <int SP, int GP, int RPT, int NE, bool G5, bool LNT, int MU, bool FWD, int SRC = 0, bool LL = false,
           int BAR = -1, int LNE = 0, typename A>
 __device__ __forceinline__ void hop_dir(Cx<real_t<SP>> (&acc)[RPT][4][3], const A &a, const bool (&act)[RPT],
                                         int r0, int nbr, int link_par, int link_site, real_t<SP> sgn, int stride,
-                                        const Cx<real_t<SP>> (*H)[2][3] = nullptr, const char *ll = nullptr) {
+                                        const Cx<real_t<SP>> (*H)[2][3] = nullptr, const char *ll = nullptr,
+                                        const Cx<real_t<SP>> *given = nullptr) {
     using R = real_t<SP>;
     // link U_mu(x) (forward, at the output site) or U_mu(x - mu) (backward, at the neighbour)
     // LNE = 9: the block's LDS copy holds all nine entries, the boundary sign folded in
     constexpr bool FULL = LL && LNE == 9;
     Cx<R> U[3][3];
-    {
+    if constexpr (SRC == 2) {
+#pragma unroll
+        for (int e = 0; e < 9; e++) U[e / 3][e % 3] = given[e];
+    } else {
         constexpr int NEU = FULL ? 9 : NE;
         constexpr int NL = LinkElems<GP, NEU>::N, CPL = LinkPack<GP>::CPL;
         Cx<R> ue[NL * CPL];
@@ -141,7 +145,7 @@ __device__ __forceinline__ void hop_dir(Cx<real_t<SP>> (&acc)[RPT][4][3], const 
 #pragma unroll
         for (int e = 0; e < NEU; e++) U[e / 3][e % 3] = ue[e];
     }
-    if constexpr (NE == 6 && !FULL) {
+    if constexpr (NE == 6 && !FULL && SRC != 2) {
         // third row of an SU(3) matrix: complex conjugate of (row 0) x (row 1)
         const Cx<R> c0 = csub(cmul(U[0][1], U[1][2]), cmul(U[0][2], U[1][1]));
         const Cx<R> c1 = csub(cmul(U[0][2], U[1][0]), cmul(U[0][0], U[1][2]));
@@ -263,17 +267,22 @@ __device__ __forceinline__ void lane_nbr(Cx<real_t<SP>> (&H)[RPT][2][3], const C
     __builtin_amdgcn_sched_barrier(0);
 }
 
+__device__ __forceinline__ double fma_dot(double acc, double a, double b, double c, double d) {
+    return fma(c, d, fma(a, b, acc));
+}
+
 // Epilogue of one output site and right-hand side: gamma5 on the hop result, the factor
-// cH, the y and z terms (with the clover modes), the store and the site's reduction terms.
+// cH, the y and z terms (with the clover modes), the result handed to put(o), and the site's
+// reduction terms.
 // PRE (bits 1, 2, 4): y, z, the dot partner w are already in yv, zv, wv (loaded by the
 // caller); the others are loaded here.  NT: the output and the operands read here are
 // streamed (non-temporal); the small-lattice kernel keeps them cached instead, since the
 // next kernel finds its whole working set in L2.
-template <int SP, bool CLV, int PRE, bool NT = true>
-__device__ __forceinline__ void hop_finish(const HopArgs &a, int i, bool valid, int rhs,
-                                           const Cx<real_t<SP>> (&acc)[4][3], Cx<real_t<SP>> (&yv)[12],
-                                           Cx<real_t<SP>> (&zv)[12], Cx<real_t<SP>> (&wv)[12], double (&red)[3],
-                                           int stride) {
+template <int SP, bool CLV, int PRE, bool NT, typename A, typename PUT>
+__device__ __forceinline__ void hop_put(const A &a, int i, bool valid, int rhs,
+                                        const Cx<real_t<SP>> (&acc)[4][3], Cx<real_t<SP>> (&yv)[12],
+                                        Cx<real_t<SP>> (&zv)[12], Cx<real_t<SP>> (&wv)[12], double (&red)[3],
+                                        int stride, PUT &&put) {
     using R = real_t<SP>;
     constexpr int CP = SP == P64 ? P64 : P32;  // storage precision of clover blocks
     const R cH = (R)a.cH[rhs];
@@ -308,23 +317,36 @@ __device__ __forceinline__ void hop_finish(const HopArgs &a, int i, bool valid, 
 #pragma unroll
         for (int k = 0; k < 12; k++) o[k] = cadd(o[k], cscale(zv[k], cz));
     }
-    if (valid && !a.nostore) store_site<SP, R, NT>(a.out, stride, rhs, i, o);
+    if (valid && !a.nostore) put(o);
     if (!valid || a.red == RED_NONE) return;
+    // (multiply-adds written out: which product the compiler would fuse differs from kernel to
+    // kernel, and every kernel that does this step must give the same bits)
     if (a.red == RED_NORM2) {
-        for (int k = 0; k < 12; k++) red[0] += (double)o[k].re * o[k].re + (double)o[k].im * o[k].im;
+        for (int k = 0; k < 12; k++) red[0] = fma_dot(red[0], o[k].re, o[k].re, o[k].im, o[k].im);
     } else if (a.red == RED_DOT) {
         if (!(PRE & 4)) load_site<SP, R, NT>(wv, a.w, stride, rhs, i);
         for (int k = 0; k < 12; k++) {  // <w, o> = sum conj(w) o
-            red[0] += (double)wv[k].re * o[k].re + (double)wv[k].im * o[k].im;
-            red[1] += (double)wv[k].re * o[k].im - (double)wv[k].im * o[k].re;
+            red[0] = fma_dot(red[0], wv[k].re, o[k].re, wv[k].im, o[k].im);
+            red[1] = fma_dot(red[1], wv[k].re, o[k].im, -wv[k].im, o[k].re);
         }
     } else {
         for (int k = 0; k < 12; k++) {  // <o, y> and |o|^2
-            red[0] += (double)o[k].re * yv[k].re + (double)o[k].im * yv[k].im;
-            red[1] += (double)o[k].re * yv[k].im - (double)o[k].im * yv[k].re;
-            red[2] += (double)o[k].re * o[k].re + (double)o[k].im * o[k].im;
+            red[0] = fma_dot(red[0], o[k].re, yv[k].re, o[k].im, yv[k].im);
+            red[1] = fma_dot(red[1], o[k].re, yv[k].im, -o[k].im, yv[k].re);
+            red[2] = fma_dot(red[2], o[k].re, o[k].re, o[k].im, o[k].im);
         }
     }
+}
+
+// The same with the result stored in the field a.out.
+template <int SP, bool CLV, int PRE, bool NT = true>
+__device__ __forceinline__ void hop_finish(const HopArgs &a, int i, bool valid, int rhs,
+                                           const Cx<real_t<SP>> (&acc)[4][3], Cx<real_t<SP>> (&yv)[12],
+                                           Cx<real_t<SP>> (&zv)[12], Cx<real_t<SP>> (&wv)[12], double (&red)[3],
+                                           int stride) {
+    using R = real_t<SP>;
+    hop_put<SP, CLV, PRE, NT>(a, i, valid, rhs, acc, yv, zv, wv, red, stride,
+                              [&](const Cx<R> (&o)[12]) { store_site<SP, R, NT>(a.out, stride, rhs, i, o); });
 }
 
 // With the wave split all waves of a block work on the same 64 sites, so each link of the

@@ -439,11 +439,7 @@ bool hop_pinned(wilson_ctx *ctx) {
     return ctx->forced;
 }
 
-int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes) {
-    if (a.nrhs < 1 || a.nrhs > kMaxRhs) throw Error(WILSON_INVALID_ARG, "nrhs out of range");
-    if (a.out.data == a.in.data || (a.has_y && a.out.data == a.y.data) || (a.has_z && a.out.data == a.z.data))
-        throw Error(WILSON_INVALID_ARG, "hop output aliases an input");
-    if (a.clov_mode != CLV_NONE && a.clov == nullptr) throw Error(WILSON_INVALID_ARG, "clover blocks missing");
+LaunchCfg hop_config(wilson_ctx *ctx, const HopArgs &a) {
     hop_pinned(ctx);
     LaunchCfg cfg;
     const wilson_ctx::HotKey hk = {a.in.prec, a.gprec, a.recon, rhs_class(a.nrhs), {a.g.L[0], a.g.L[1], a.g.L[2], a.g.L[3]}};
@@ -480,7 +476,15 @@ int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes) {
     }
     // a stored or pinned shape may not suit this launch (clover epilogue, RHS count): keep
     // its order and block, fit the RHS split
-    cfg = fit_cfg(a, cfg);
+    return fit_cfg(a, cfg);
+}
+
+int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes) {
+    if (a.nrhs < 1 || a.nrhs > kMaxRhs) throw Error(WILSON_INVALID_ARG, "nrhs out of range");
+    if (a.out.data == a.in.data || (a.has_y && a.out.data == a.y.data) || (a.has_z && a.out.data == a.z.data))
+        throw Error(WILSON_INVALID_ARG, "hop output aliases an input");
+    if (a.clov_mode != CLV_NONE && a.clov == nullptr) throw Error(WILSON_INVALID_ARG, "clover blocks missing");
+    const LaunchCfg cfg = hop_config(ctx, a);
     ctx->hop_launch_count++;
     ctx->bytes_issued += algorithmic_bytes;
     ctx->flops_issued += (a.clov_mode != CLV_NONE ? 1896.0 : 1320.0) * a.g.Vh * a.nrhs;

@@ -176,6 +176,7 @@ struct wilson_ctx {
     // host resources lent to solves whose device memory the caller provides (created with
     // the context, so those solves allocate nothing themselves)
     wl::SolveHostRes lend;
+    int small_blocks[2][2] = {{-1, -1}, {-1, -1}};  // blocks of the one-launch solve the device holds (FP64 / FP32, 12 / 18 link reals)
     void *scratch = nullptr;         // device address of the no-allocation solve's array on this device
     hipStream_t capture_stream = nullptr;  // stream that iteration chunks are captured on (HIP graphs)
     bool no_tune = false;            // set for the duration of a call that must not tune
@@ -200,6 +201,8 @@ namespace wl {
 // algorithmic_bytes is the per-launch byte count used for achieved-bandwidth figures.
 // Returns the number of blocks launched (the row length of the partials it wrote).
 int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes);
+// The launch shape a hop takes (pinned, tuned now or earlier, or the default).
+LaunchCfg hop_config(wilson_ctx *ctx, const HopArgs &a);
 // Whether a launch shape is pinned for this context (WILSON_HOP_CFG).
 bool hop_pinned(wilson_ctx *ctx);
 // Launch a BLAS kernel (timed as class BLAS).

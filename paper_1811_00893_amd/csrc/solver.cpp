@@ -123,6 +123,7 @@ class EoCore : public EoMem {
     // bookkeeping of one replay
     bool graphs = false;  // set per call
     bool prefin = false;  // vector kernels may run the finalize before them (set per call)
+    bool small = false;   // BiCGStab solves may run in one launch (set per call)
     // device addresses a captured chunk reads from the gauge field (links of every
     // precision, clover blocks) and its link storage: a cached workspace may be bound to
     // another field, or to a field loaded again at the same host address
@@ -442,6 +443,7 @@ class EoCore : public EoMem {
                 run_blas(BL_COPY_NORM, a, vec_bytes(P, 2));
             }
             finalize(FIN_BICG_INIT, 1, nb, sin(), PH_RUN);
+            if (small_fits()) return small_solve(x, maxiter);
             for (Spinor f : {p.f, v.f, t.f}) WL_HIP(launch_zero(V(f), g, nk, ctx->stream));
         } else if (method == WILSON_SOLVER_BLOCK_BICGSTAB_EO) {
             // R = rhs - A X (or rhs), P = R, R~ = R with the column norms, then one phase
@@ -514,6 +516,66 @@ class EoCore : public EoMem {
             }
         }
         return read_states(sin());
+    }
+
+    // Whether this solve's iterations can run in one cooperative launch (small_solve.hip): the
+    // lattices whose hops split the directions over waves (the kernel adds them in that order)
+    // and whose partial rows one wave sums, FP64 or FP32, no clover term, every block resident,
+    // nothing asked for that needs the separate launches (per-launch timing, graphs, separate
+    // finalizes).  8^4 FP64: 58 us per iteration in nine launches, 32 in one; whole solves, us,
+    // separate launches against one: 8^4 FP64 1 RHS 1230 / 763, 8 RHS 1353 / 895, mixed FP32
+    // 1519 / 887; 8^2x16^2 (128 tiles) FP64 1478 / 1180, mixed 1596 / 1116.
+    bool small_fits() {
+        const int tiles = (g.Vh + 63) / 64;
+        if (!small || !prefin || graphs || ctx->timing || G->has_clover() || (P != P64 && P != P32) || PX != P ||
+            tiles > kPreFinMax || blas_nblocks(g, P) > kPreFinMax)
+            return false;
+        int &cap = ctx->small_blocks[P == P64 ? 0 : 1][G->recon == 12 ? 0 : 1];
+        if (cap < 0) cap = small_max_blocks(P, G->recon);
+        return tiles * nk <= cap && hop_config(ctx, hop_args(1, tmp.f, p.f)).dsplit;
+    }
+
+    std::vector<RhsState> small_solve(Spinor x, int maxiter) {
+        SmallArgs a;
+        std::memset(&a, 0, sizeof a);
+        a.g = g;
+        a.nrhs = nk;
+        a.tiles = (g.Vh + 63) / 64;
+        a.gauge = links(P);
+        a.r = V(r.f); a.rh = V(rh.f); a.p = V(p.f); a.v = V(v.f); a.s = V(s.f); a.x = V(x); a.tmp = V(tmp.f);
+        a.scratch = static_cast<char *>(V(t.f).data);  // t stays in registers: its field holds the exchanged sums
+        a.scratch_stride = 12 * spinor_plane_bytes(P, g);
+        a.state = S(sin());
+        for (int k = 0; k < nk; k++) a.cH[k] = -kap(k) * kap(k);
+        a.first = 1;
+        // (the iterations of one launch are bounded, so that no kernel runs for long)
+        constexpr int kChunk = 1024;
+        for (int done = 0;;) {
+            WL_HIP(launch_zero(V(t.f), g, nk, ctx->stream));
+            a.iters = std::min(maxiter - done, kChunk);
+            WL_HIP(launch_bicg_small(a, P, G->recon, ctx->stream));
+            std::vector<RhsState> st = read_states(sin());
+            done += a.iters;
+            a.first = 0;
+            bool running = false;
+            int most = 0;
+            for (const RhsState &q : st) {
+                if (q.phase == PH_FAIL && q.fail == FAIL_DEVICE)
+                    throw Error(WILSON_DEVICE_ERROR, "the blocks of a one-launch solve lost each other");
+                running |= q.phase == PH_RUN;
+                most = std::max(most, q.iter);
+            }
+            if (running && done < maxiter) continue;
+            // the launches it stands for
+            HopArgs h1 = hop_args(1, tmp.f, p.f), h2 = hop_args(0, v.f, tmp.f);
+            h2.has_y = 1;
+            const double plain = hop_bytes(h1), with_y = hop_bytes(h2);
+            h2.red = RED_DOT;
+            ctx->hop_launch_count += 4 * most;
+            ctx->bytes_issued += most * (2 * plain + with_y + hop_bytes(h2) + vec_bytes(P, 4 + 3 + 7));
+            ctx->flops_issued += 4.0 * most * 1320.0 * g.Vh * nk;
+            return st;
+        }
     }
 
     void iterate(Spinor x, RhsState *mir) {
@@ -733,6 +795,7 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
     const Geom &g = C.g;
     C.graphs = prm.graphs && !prm.no_tune && graphs_enabled() && g.Vh <= kGraphMaxVh;
     C.prefin = prefin_enabled();
+    C.small = !prm.reliable;  // (reliable updates resume from p and v)
     C.select(0, nrhs);
     C.kappa.assign(C.nrhs, 0.0);
     std::copy(kappa, kappa + nrhs, C.kappa.begin());
