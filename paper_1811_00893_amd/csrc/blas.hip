@@ -37,7 +37,7 @@ template <> struct OpShape<BL_XR_UPDATE> { static constexpr int LD = SA | SB | S
 template <> struct OpShape<BL_COPY_NORM> { static constexpr int LD = SB, ST = SA, NV = 1; };
 template <> struct OpShape<BL_CG_XR> { static constexpr int LD = SA | SB | SC | SX, ST = SB | SX, NV = 1; };
 template <> struct OpShape<BL_CG_P> { static constexpr int LD = SA | SB, ST = SA, NV = 0; };
-template <> struct OpShape<BL_NORM2> { static constexpr int LD = SA, ST = 0, NV = 1; };
+template <> struct OpShape<BL_START> { static constexpr int LD = SB, ST = SA | SC | SE, NV = 1; };
 
 // N complex numbers of every operand slot (a whole site, or one 16-byte element).
 template <int N, typename R, typename RX>
@@ -70,11 +70,13 @@ __device__ __forceinline__ void blas_math(const RhsState *st, Opnds<N, R, RX> &o
         const Cx<RX> alpha = {(RX)st->alpha_re, (RX)st->alpha_im};
         const Cx<RX> omega_x = {(RX)st->omega_re, (RX)st->omega_im};
         const Cx<R> omega = {(R)st->omega_re, (R)st->omega_im};
+        const bool half = st->phase == PH_SCONV;
 #pragma unroll
         for (int k = 0; k < N; k++) {
             const Cx<RX> pk = {(RX)o.a[k].re, (RX)o.a[k].im}, sk = {(RX)o.b[k].re, (RX)o.b[k].im};
             o.x[k] = cadd(o.x[k], cadd(cmul(alpha, pk), cmul(omega_x, sk)));
-            const Cx<R> r = csub(o.b[k], cmul(omega, o.d[k]));
+            // converged on s: omega is zero, and t may never have been written
+            const Cx<R> r = half ? o.b[k] : csub(o.b[k], cmul(omega, o.d[k]));
             o.c[k] = r;
             red[0] += norm2_of(r);
             red[1] += (double)o.e[k].re * r.re + (double)o.e[k].im * r.im;  // <rhat, r>
@@ -99,9 +101,12 @@ __device__ __forceinline__ void blas_math(const RhsState *st, Opnds<N, R, RX> &o
         const R beta = (R)st->beta_re;
 #pragma unroll
         for (int k = 0; k < N; k++) o.a[k] = cadd(o.b[k], cscale(o.a[k], beta));
-    } else if constexpr (OP == BL_NORM2) {
+    } else if constexpr (OP == BL_START) {
 #pragma unroll
-        for (int k = 0; k < N; k++) red[0] += norm2_of(o.a[k]);
+        for (int k = 0; k < N; k++) {
+            o.a[k] = o.c[k] = o.e[k] = o.b[k];
+            red[0] += norm2_of(o.b[k]);
+        }
     }
 }
 
@@ -143,6 +148,7 @@ __global__ void __launch_bounds__(kElemBlock) blas_elem_kernel(const BlasArgs a,
         if constexpr (S::ST & SA) st_elem<P, R, NT>(const_cast<gchar *>(splane(a.a.data, plane, stride)), off, o.a);
         if constexpr (S::ST & SB) st_elem<P, R, NT>(const_cast<gchar *>(splane(a.b.data, plane, stride)), off, o.b);
         if constexpr (S::ST & SC) st_elem<P, R, NT>(const_cast<gchar *>(splane(a.c.data, plane, stride)), off, o.c);
+        if constexpr (S::ST & SE) st_elem<P, R, NT>(const_cast<gchar *>(splane(a.e.data, plane, stride)), off, o.e);
         if constexpr (S::ST & SX) st_elem<P, R, NT>(const_cast<gchar *>(splane(a.x.data, plane, stride)), off, o.x);
     } else {
         red[0] = red[1] = red[2] = 0.0;
@@ -189,6 +195,7 @@ __global__ void __launch_bounds__(kSiteBlock) blas_site_kernel(const BlasArgs a)
         if constexpr (S::ST & SA) store_site<PK, R, NT>(a.a, stride, rhs, i, o.a);
         if constexpr (S::ST & SB) store_site<PK, R, NT>(a.b, stride, rhs, i, o.b);
         if constexpr (S::ST & SC) store_site<PK, R, NT>(a.c, stride, rhs, i, o.c);
+        if constexpr (S::ST & SE) store_site<PK, R, NT>(a.e, stride, rhs, i, o.e);
         if constexpr (S::ST & SX) store_site<PX, RX, NT>(a.x, stride, rhs, i, o.x);
     } else {
         red[0] = red[1] = red[2] = 0.0;
@@ -275,7 +282,7 @@ hipError_t launch_blas(int op, const BlasArgs &a, hipStream_t s) {
         case BL_COPY_NORM: return launch_op<BL_COPY_NORM>(pk, px, a, s);
         case BL_CG_XR: return launch_op<BL_CG_XR>(pk, px, a, s);
         case BL_CG_P: return launch_op<BL_CG_P>(pk, px, a, s);
-        case BL_NORM2: return launch_op<BL_NORM2>(pk, px, a, s);
+        case BL_START: return launch_op<BL_START>(pk, px, a, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -285,6 +292,44 @@ hipError_t launch_blas(int op, const BlasArgs &a, hipStream_t s) {
 // the scalar step (finalize.h).  Rows a vector kernel could finalize (up to kPreFinMax
 // partials) take one wave, exactly as that kernel does (PreFin); longer rows 256 threads,
 // beyond 4096 partials 1024 (each thread with the same grouping, then the waves in order).
+// What it costs is latency (one block, 5-10 us of a large lattice's iteration four times), so
+// nothing waits that need not: the rows of all values are read together, and before the
+// phase is known; the state is copied to LDS meanwhile and stepped there.
+template <int NV>
+__device__ __forceinline__ void sum_rows(const double *p, int n, double (&v)[3]) {
+    // 8 independent accumulators per value keep that many loads in flight per thread; the
+    // grouping is fixed, so the sum is the same on every run
+    double acc[NV][8];
+#pragma unroll
+    for (int k = 0; k < NV; k++)
+#pragma unroll
+        for (int u = 0; u < 8; u++) acc[k][u] = 0.0;
+    const int bd = blockDim.x;
+    int j0 = threadIdx.x;
+    for (; j0 + 7 * bd < n; j0 += 8 * bd) {
+        double w[NV][8];
+#pragma unroll
+        for (int k = 0; k < NV; k++)
+#pragma unroll
+            for (int u = 0; u < 8; u++) w[k][u] = p[(size_t)k * n + j0 + u * bd];
+#pragma unroll
+        for (int k = 0; k < NV; k++)
+#pragma unroll
+            for (int u = 0; u < 8; u++) acc[k][u] += w[k][u];
+    }
+    double w[NV][8];
+#pragma unroll
+    for (int k = 0; k < NV; k++)
+#pragma unroll
+        for (int u = 0; u < 8; u++) w[k][u] = j0 + u * bd < n ? p[(size_t)k * n + j0 + u * bd] : 0.0;
+#pragma unroll
+    for (int k = 0; k < NV; k++) {
+#pragma unroll
+        for (int u = 0; u < 8; u++) acc[k][u] += w[k][u];
+        v[k] = ((acc[k][0] + acc[k][1]) + (acc[k][2] + acc[k][3])) + ((acc[k][4] + acc[k][5]) + (acc[k][6] + acc[k][7]));
+    }
+}
+
 template <int OP>
 __global__ void __launch_bounds__(1024) finalize_kernel(const double *partials, int nv, int nblocks,
                                                        RhsState *state, int run_mask, RhsState *mirror) {
@@ -293,31 +338,38 @@ __global__ void __launch_bounds__(1024) finalize_kernel(const double *partials, 
         fin_rhs_wave(OP, partials, nv, nblocks, rhs, state, run_mask, mirror);
         return;
     }
-    RhsState *st = &state[rhs];
-    if (st->phase & run_mask) {
-        __shared__ double tot[3];
-        double v[3] = {0.0, 0.0, 0.0};
-        for (int k = 0; k < nv; k++) {
-            // 8 independent accumulators keep 8 loads in flight per thread; the grouping
-            // is fixed, so the sum is the same on every run
-            const double *p = partials + ((size_t)rhs * nv + k) * nblocks;
-            double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            const int step = blockDim.x * 8;
-            int j0 = threadIdx.x;
-            for (; j0 + 7 * (int)blockDim.x < nblocks; j0 += step) {
-#pragma unroll
-                for (int u = 0; u < 8; u++) acc[u] += p[j0 + u * blockDim.x];
-            }
-            for (int u = 0; u < 8; u++) {
-                const int j = j0 + u * blockDim.x;
-                if (j < nblocks) acc[u] += p[j];
-            }
-            v[k] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+    __shared__ RhsState loc;
+    __shared__ double tot[3];
+    if (threadIdx.x == 0) loc = state[rhs];
+    double v[3] = {0.0, 0.0, 0.0};
+    const double *row = partials + (size_t)rhs * nv * nblocks;
+    if (nv == 1) sum_rows<1>(row, nblocks, v);
+    else if (nv == 2) sum_rows<2>(row, nblocks, v);
+    else sum_rows<3>(row, nblocks, v);
+    block_reduce_to<3>(v, tot, 1);  // (its barriers also order loc and tot)
+    if (threadIdx.x == 0) {
+        if (loc.phase & run_mask) {
+            fin_op<OP>(&loc, tot[0], tot[1], tot[2]);
+            state[rhs] = loc;
         }
-        block_reduce_to<3>(v, tot, 1);
-        if (threadIdx.x == 0) fin_op<OP>(st, tot[0], tot[1], tot[2]);
+        if (mirror) mirror[rhs] = loc;
     }
-    if (mirror && threadIdx.x == 0) mirror[rhs] = *st;
+}
+
+// Fresh states: everything zero but the phases and thresholds (launch arguments, so nothing is
+// copied from the host and nothing has to wait for such a copy).
+__global__ void init_states_kernel(RhsState *st, const StateInit init) {
+    const int k = threadIdx.x;
+    if (k >= init.n) return;
+    RhsState s = {};
+    s.phase = init.phase[k];
+    s.stop2 = init.stop2[k];
+    st[k] = s;
+}
+hipError_t launch_init_states(RhsState *st, const StateInit &init, hipStream_t s) {
+    if (init.n < 1 || init.n > kMaxRhs) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(init_states_kernel, dim3(1), dim3(64), 0, s, st, init);
+    return hipGetLastError();
 }
 
 hipError_t launch_finalize(int op, const double *partials, int nvals, int nblocks, int nrhs, RhsState *state,
@@ -339,7 +391,6 @@ hipError_t launch_finalize(int op, const double *partials, int nvals, int nblock
         FIN_CASE(FIN_CG_ALPHA)
         FIN_CASE(FIN_CG_R)
         FIN_CASE(FIN_CG_BETA)
-        FIN_CASE(FIN_ADD_AUX)
         FIN_CASE(FIN_BLOCK_TS)
         default: return hipErrorInvalidValue;
     }

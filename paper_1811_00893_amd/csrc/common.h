@@ -117,7 +117,6 @@ enum FinOp : int {
     FIN_CG_ALPHA,       // alpha = zz / |w|^2
     FIN_CG_R,           // r2 after the update; iteration count; convergence
     FIN_CG_BETA,        // beta = |z'|^2 / zz; zz = |z'|^2
-    FIN_ADD_AUX,        // aux += value 0
     FIN_BLOCK_TS        // omega = <t,s> (values 0, 1), aux = |t|^2 (value 2), summed over the block later
 };
 
@@ -280,7 +279,7 @@ enum BlasOp : int {
     BL_COPY_NORM,     // a = copy of b; |b|^2
     BL_CG_XR,         // x += alpha p(a); r(b) -= alpha w(c); |r|^2
     BL_CG_P,          // p(a) = z(b) + beta p
-    BL_NORM2          // |a|^2
+    BL_START          // a = c = e = b; |b|^2
 };
 // partial sums one BLAS launch leaves per RHS and value (prec: storage precision of its operands)
 int blas_nblocks(const Geom &g, int prec);
@@ -288,6 +287,13 @@ hipError_t launch_blas(int op, const BlasArgs &a, hipStream_t s);
 hipError_t launch_finalize(int op, const double *partials, int nvals, int nblocks, int nrhs, RhsState *state,
                            int run_mask, hipStream_t s, RhsState *mirror = nullptr);
 hipError_t launch_zero(const Spinor &f, const Geom &g, int nrhs, hipStream_t s);
+// States of n right-hand sides set to zero but for these.
+struct StateInit {
+    int n;
+    int phase[kMaxRhs];
+    double stop2[kMaxRhs];
+};
+hipError_t launch_init_states(RhsState *st, const StateInit &init, hipStream_t s);
 
 // BiCGStab iterations on M_ee in one cooperative launch (small lattices, no clover term): one
 // block per 64-site tile and right-hand side.  Fields hold nrhs right-hand sides; r, rhat and x
@@ -313,7 +319,10 @@ hipError_t launch_bicg_small(const SmallArgs &p, int prec, int recon, hipStream_
 // Layout / precision conversion.
 // canonical complex128 [rhs][V][4][3]  <->  parity fields of precision f.prec: both parities
 // in one pass (split, join), or one of them.
-hipError_t launch_split(Spinor fe, Spinor fo, const double *canon, const Geom &g, int nrhs, hipStream_t s);
+// (split with partials: one |.|^2 partial per right-hand side and block, rows of split_nblocks)
+int split_nblocks(const Geom &g);
+hipError_t launch_split(Spinor fe, Spinor fo, const double *canon, const Geom &g, int nrhs, hipStream_t s,
+                        double *partials = nullptr);
 hipError_t launch_split_one(Spinor f, const double *canon, const Geom &g, int par, int nrhs, hipStream_t s);
 hipError_t launch_join(double *canon, Spinor fe, Spinor fo, const Geom &g, int nrhs, hipStream_t s);
 hipError_t launch_join_one(double *canon, Spinor f, const Geom &g, int par, int nrhs, hipStream_t s);

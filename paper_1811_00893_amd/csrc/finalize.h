@@ -19,8 +19,6 @@ __device__ __forceinline__ void fin_op(RhsState *st, const double a0, const doub
     };
     if constexpr (OP == FIN_STORE_AUX) {
         st->aux = a0;
-    } else if constexpr (OP == FIN_ADD_AUX) {
-        st->aux += a0;
     } else if constexpr (OP == FIN_BICG_INIT) {
         st->r2 = a0;
         st->rhat2 = a0;
@@ -129,7 +127,6 @@ static __device__ __noinline__ void fin_op_rt(int op, RhsState *st, double a0, d
         FIN_RT(FIN_CG_ALPHA)
         FIN_RT(FIN_CG_R)
         FIN_RT(FIN_CG_BETA)
-        FIN_RT(FIN_ADD_AUX)
         FIN_RT(FIN_BLOCK_TS)
         default: break;
     }

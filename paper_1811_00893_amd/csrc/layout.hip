@@ -37,8 +37,9 @@ __device__ __forceinline__ int full_site(const Geom &g, int i, int par, int *t_o
 //     access.
 constexpr int kRow = 13;  // padded LDS row: elements of one site
 
-template <int P>
-__global__ void __launch_bounds__(256) split_kernel(Spinor fe, Spinor fo, const double2 *canon, Geom g) {
+template <int P, bool NORM>
+__global__ void __launch_bounds__(256) split_kernel(Spinor fe, Spinor fo, const double2 *canon, Geom g,
+                                                    double *partials) {
     using R = real_t<P>;
     __shared__ __align__(16) Cx<R> buf[256 * kRow];
     const int tid = threadIdx.x, rhs = blockIdx.y;
@@ -55,12 +56,19 @@ __global__ void __launch_bounds__(256) split_kernel(Spinor fe, Spinor fo, const 
     }
     __syncthreads();
     const int par = __builtin_amdgcn_readfirstlane(tid >> 7), l = tid & 127;
-    if (l >= n) return;
-    const SiteXY c = cb_coords(g, i0 + l, par);
-    Cx<R> v[12];
+    double red[1] = {0.0};
+    if (l < n) {
+        const SiteXY c = cb_coords(g, i0 + l, par);
+        Cx<R> v[12];
 #pragma unroll
-    for (int k = 0; k < 12; k++) v[k] = buf[(2 * l + c.b) * kRow + k];
-    store_site<P, R>(par ? fo : fe, g.stride, rhs, i0 + l, v);
+        for (int k = 0; k < 12; k++) v[k] = buf[(2 * l + c.b) * kRow + k];
+        if constexpr (NORM) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) red[0] += (double)v[k].re * v[k].re + (double)v[k].im * v[k].im;
+        }
+        store_site<P, R>(par ? fo : fe, g.stride, rhs, i0 + l, v);
+    }
+    if constexpr (NORM) block_reduce_to<1>(red, partials + (size_t)rhs * gridDim.x + blockIdx.x, 1);
 }
 
 template <int P>
@@ -334,14 +342,20 @@ __global__ void check_finite_kernel(const double *p, size_t n, int *flag) {
 // ---------------------------------------------------------------------------------
 static inline dim3 site_grid(const Geom &g, int ny) { return dim3((g.Vh + 255) / 256, ny); }
 
-hipError_t launch_split(Spinor fe, Spinor fo, const double *canon, const Geom &g, int nrhs, hipStream_t s) {
-    if (fe.prec != fo.prec) return hipErrorInvalidValue;
-    const dim3 grid((g.Vh + 127) / 128, nrhs), block(256);
+int split_nblocks(const Geom &g) { return (g.Vh + 127) / 128; }
+
+hipError_t launch_split(Spinor fe, Spinor fo, const double *canon, const Geom &g, int nrhs, hipStream_t s,
+                        double *partials) {
+    if (fe.prec != fo.prec || (partials && fe.prec != P64)) return hipErrorInvalidValue;
+    const dim3 grid(split_nblocks(g), nrhs), block(256);
     const double2 *c = reinterpret_cast<const double2 *>(canon);
     switch (fe.prec) {
-        case P64: hipLaunchKernelGGL(split_kernel<P64>, grid, block, 0, s, fe, fo, c, g); break;
-        case P32: hipLaunchKernelGGL(split_kernel<P32>, grid, block, 0, s, fe, fo, c, g); break;
-        case P16: hipLaunchKernelGGL(split_kernel<P16>, grid, block, 0, s, fe, fo, c, g); break;
+        case P64:
+            if (partials) hipLaunchKernelGGL((split_kernel<P64, true>), grid, block, 0, s, fe, fo, c, g, partials);
+            else hipLaunchKernelGGL((split_kernel<P64, false>), grid, block, 0, s, fe, fo, c, g, partials);
+            break;
+        case P32: hipLaunchKernelGGL((split_kernel<P32, false>), grid, block, 0, s, fe, fo, c, g, partials); break;
+        case P16: hipLaunchKernelGGL((split_kernel<P16, false>), grid, block, 0, s, fe, fo, c, g, partials); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -361,7 +375,7 @@ hipError_t launch_split_one(Spinor f, const double *canon, const Geom &g, int pa
 
 hipError_t launch_join(double *canon, Spinor fe, Spinor fo, const Geom &g, int nrhs, hipStream_t s) {
     if (fe.prec != fo.prec) return hipErrorInvalidValue;
-    const dim3 grid((g.Vh + 127) / 128, nrhs), block(256);
+    const dim3 grid(split_nblocks(g), nrhs), block(256);
     double2 *c = reinterpret_cast<double2 *>(canon);
     switch (fe.prec) {
         case P64: hipLaunchKernelGGL(join_kernel<P64>, grid, block, 0, s, c, fe, fo, g); break;

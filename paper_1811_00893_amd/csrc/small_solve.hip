@@ -469,7 +469,7 @@ bicg_small_kernel(const SmallArgs p) {
 #pragma unroll
                     for (int k = 0; k < CPE; k++) {
                         x[q][k] = nc::add(x[q][k], nc::add(nc::mul(alpha, pp[q][k]), nc::mul(omega, s[q][k])));
-                        r[q][k] = nc::sub(s[q][k], nc::mul(omega, t[q][k]));
+                        r[q][k] = (loc.phase & PH_SCONV) ? s[q][k] : nc::sub(s[q][k], nc::mul(omega, t[q][k]));
                         nc::dot(red, rh[q][k], r[q][k]);
                     }
                 }

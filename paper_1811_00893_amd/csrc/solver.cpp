@@ -334,17 +334,22 @@ class EoCore : public EoMem {
         return (double)nvec * g.Vh * nk * (24.0 * real_bytes(prec) + (prec == P16 ? 4.0 : 0.0));
     }
 
-    // |e|^2 + |o|^2 of FP64 fields into st[].aux
-    void norm2_full(Spinor e, Spinor o, RhsState *st) {
-        BlasArgs a = blas_args(nullptr, 0);
-        a.a = e;
-        run_blas(BL_NORM2, a, vec_bytes(e.prec, 1));
-        finalize(FIN_STORE_AUX, 1, blas_nblocks(g, e.prec), st, kAllPhases);
-        a.a = o;
-        run_blas(BL_NORM2, a, vec_bytes(o.prec, 1));
-        finalize(FIN_ADD_AUX, 1, blas_nblocks(g, o.prec), st, kAllPhases);
+    // canonical right-hand sides -> b_e, b_o, with |b|^2 in st[].aux
+    void take_rhs(const double *canon, RhsState *st) {
+        WL_HIP(launch_split(V(b_e.f), V(b_o.f), canon, g, nk, ctx->stream, part()));
+        finalize(FIN_STORE_AUX, 1, split_nblocks(g), st, kAllPhases);
     }
 
+    // fresh states of the selected range: phase[k] and stop2[k] (null: the same phase, no threshold)
+    void set_states(RhsState *dst, int phase, const std::vector<char> *active = nullptr, const double *stop2 = nullptr) {
+        StateInit in;
+        in.n = nk;
+        for (int k = 0; k < nk; k++) {
+            in.phase[k] = active && !(*active)[k] ? PH_IDLE : phase;
+            in.stop2[k] = stop2 ? stop2[k] : 0.0;
+        }
+        WL_HIP(launch_init_states(S(dst), in, ctx->stream));
+    }
     // host <-> device copies of the states of the selected range
     void upload_states(RhsState *dst, const std::vector<RhsState> &h) {
         WL_HIP(hipStreamSynchronize(ctx->stream));  // hinit may still be the source of a copy
@@ -352,17 +357,30 @@ class EoCore : public EoMem {
         WL_HIP(hipMemcpyAsync(S(dst), host->hinit.host(), sizeof(RhsState) * nk, hipMemcpyHostToDevice, ctx->stream));
     }
     std::vector<RhsState> read_states(RhsState *src) {
+        std::vector<RhsState> h(nk);
         WL_HIP(hipMemcpyAsync(host->hread.host(), S(src), sizeof(RhsState) * nk, hipMemcpyDeviceToHost, ctx->stream));
         WL_HIP(hipStreamSynchronize(ctx->stream));
         ctx->drain_timing();
-        std::vector<RhsState> h(nk);
         std::memcpy(h.data(), host->hread.host(), sizeof(RhsState) * nk);
         return h;
     }
+    // the aux values of two state arrays with one wait
+    void read_aux(RhsState *one, RhsState *two, std::vector<double> &a, std::vector<double> &b) {
+        // (the second goes through the upload buffer, which nothing reads after a wait)
+        WL_HIP(hipMemcpyAsync(host->hinit.host(), S(two), sizeof(RhsState) * nk, hipMemcpyDeviceToHost, ctx->stream));
+        const std::vector<RhsState> h = read_states(one);
+        const RhsState *t = static_cast<const RhsState *>(host->hinit.host());
+        a.resize(nk);
+        b.resize(nk);
+        for (int k = 0; k < nk; k++) {
+            a[k] = h[k].aux;
+            b[k] = t[k].aux;
+        }
+    }
 
     // b' = b_e + k H_eo b_o
-    // (clover: b'_e = b_e + k H_eo T_oo^-1 b_o)
-    void prepare_bprime() {
+    // (clover: b'_e = b_e + k H_eo T_oo^-1 b_o); norm: |b'|^2 into that array's aux
+    void prepare_bprime(RhsState *norm = nullptr) {
         Spinor src = b_o.f;
         if (G->has_clover()) {
             Spinor t = tmp64_or_scratch();
@@ -372,7 +390,9 @@ class EoCore : public EoMem {
         HopArgs a = hop_args(0, bp.f, src);
         a.has_y = 1; a.y = V(b_e.f);
         for (int k = 0; k < nk; k++) a.cH[k] = kap(k);
-        run_hop(a);
+        if (norm) a.red = RED_NORM2;
+        const int nb = run_hop(a);
+        if (norm) finalize(FIN_STORE_AUX, 1, nb, norm, kAllPhases);
     }
     // x_o = b_o + k H_oe x_e  (clover: x_o = T_oo^-1 (b_o + k H_oe x_e))
     void reconstruct() {
@@ -385,8 +405,10 @@ class EoCore : public EoMem {
         }
         run_hop(a);
     }
-    // |b - D x|^2 of the full system into sout()[].aux (nothing stored)
+    // |b - D x|^2 of the full system into sout()[].aux (nothing stored); the two parities'
+    // partials share one row
     void true_residual2() {
+        int nb = 0;
         for (int par = 0; par < 2; par++) {
             HopArgs a = hop_args(par, par ? tmp64_or_scratch() : tmp64_or_scratch(), par ? x_e.f : x_o.f);
             a.nostore = 1;
@@ -398,13 +420,26 @@ class EoCore : public EoMem {
                 a.clov_mode = CLV_Z;
             }
             a.red = RED_NORM2;
-            const int nb = run_hop(a);
-            finalize(par ? FIN_ADD_AUX : FIN_STORE_AUX, 1, nb, sout(), kAllPhases);
+            if (par == 0) nb = hop_nblocks(a, hop_config(ctx, a));
+            a.pstride = 2 * nb;
+            a.partials = part() + par * nb;
+            if (run_hop(a) != nb) throw Error(WILSON_DEVICE_ERROR, "the hops of one residual differ in shape");
         }
+        finalize(FIN_STORE_AUX, 1, 2 * nb, sout(), kAllPhases);
     }
     Spinor tmp64_or_scratch() {
         // output of a no-store hop is never written; any distinct FP64 field serves as the descriptor
         return mixed ? tmp64.f : (P == P64 ? tmp.f : tmp64.f);
+    }
+
+    // r = rhs - M x (or rhs), rhat = p = r in one pass, |r|^2 in the partials
+    void start_fields(bool use_x0, Spinor x, Spinor rhs) {
+        Spinor none;
+        if (use_x0) apply_M(r.f, x, tmp.f, false, RED_NONE, none, sin(), PH_RUN, &rhs);
+        BlasArgs a = blas_args(sin(), PH_RUN);
+        a.a = r.f; a.c = p.f; a.e = rh.f;
+        a.b = use_x0 ? r.f : rhs;
+        run_blas(BL_START, a, vec_bytes(P, 4));
     }
 
     // ---- inner Krylov solve on M_ee x = rhs (rhs in P, x in PX) ----
@@ -416,49 +451,21 @@ class EoCore : public EoMem {
     std::vector<RhsState> inner_solve(Spinor rhs, Spinor x, bool use_x0, const std::vector<char> &active,
                                       const std::vector<double> &stop2, int maxiter, int poll_every,
                                       const std::vector<RhsState> *resume = nullptr) {
-        std::vector<RhsState> h(nk);
-        for (int k = 0; k < nk; k++) {
-            std::memset(&h[k], 0, sizeof(RhsState));
-            h[k].phase = active[k] ? PH_RUN : PH_IDLE;
-            h[k].stop2 = stop2[k];
-        }
-        if (resume) h = *resume;
-        upload_states(sin(), h);
+        if (resume) upload_states(sin(), *resume);
+        else set_states(sin(), PH_RUN, &active, stop2.data());
         const int nb = blas_nblocks(g, P);
         Spinor none;
         if (resume) {
             if (method != WILSON_SOLVER_BICGSTAB_EO) throw Error(WILSON_INVALID_ARG, "only BiCGStab resumes");
         } else if (method == WILSON_SOLVER_BICGSTAB_EO) {
-            // r = rhs - M x  (or rhs), rhat = r
-            if (use_x0) {
-                apply_M(r.f, x, tmp.f, false, RED_NONE, none, sin(), PH_RUN, &rhs);
-                BlasArgs a = blas_args(sin(), PH_RUN);
-                a.a = rh.f; a.b = r.f;
-                run_blas(BL_COPY_NORM, a, vec_bytes(P, 2));
-            } else {
-                BlasArgs a = blas_args(sin(), PH_RUN);
-                a.a = r.f; a.b = rhs;
-                run_blas(BL_COPY_NORM, a, vec_bytes(P, 2));
-                a.a = rh.f; a.b = rhs;
-                run_blas(BL_COPY_NORM, a, vec_bytes(P, 2));
-            }
+            // r = rhs - M x  (or rhs), rhat = p = r: the first iteration starts from p as it is
+            start_fields(use_x0, x, rhs);
             finalize(FIN_BICG_INIT, 1, nb, sin(), PH_RUN);
             if (small_fits()) return small_solve(x, maxiter);
-            for (Spinor f : {p.f, v.f, t.f}) WL_HIP(launch_zero(V(f), g, nk, ctx->stream));
         } else if (method == WILSON_SOLVER_BLOCK_BICGSTAB_EO) {
             // R = rhs - A X (or rhs), P = R, R~ = R with the column norms, then one phase
             // for the whole block (it runs while any column misses its threshold)
-            BlasArgs a = blas_args(sin(), PH_RUN);
-            if (use_x0) {
-                apply_M(r.f, x, tmp.f, false, RED_NONE, none, sin(), PH_RUN, &rhs);
-            } else {
-                a.a = r.f; a.b = rhs;
-                run_blas(BL_COPY_NORM, a, vec_bytes(P, 2));
-            }
-            a.a = p.f; a.b = r.f;
-            run_blas(BL_COPY_NORM, a, vec_bytes(P, 2));
-            a.a = rh.f; a.b = r.f;
-            run_blas(BL_COPY_NORM, a, vec_bytes(P, 2));
+            start_fields(use_x0, x, rhs);
             finalize(FIN_BICG_INIT, 1, nb, sin(), PH_RUN);
             run_block(BK_SOLVE, BS_INIT, block_args(sin()), 0.0);
         } else {
@@ -478,8 +485,11 @@ class EoCore : public EoMem {
             a.a = p.f; a.b = s.f;
             run_blas(BL_COPY_NORM, a, vec_bytes(P, 2));
         }
-        // enqueue iterations ahead of the host; poll `lag` iterations behind
-        const int lag = 2;
+        // Enqueue iterations ahead of the host, which polls `lag` iterations behind the newest but
+        // one.  The iterations in flight when the solve converges run masked, but still launch
+        // (11 kernels, 5-25 us each with the lattice's blocks): where an iteration takes longer
+        // than the host needs to enqueue one (~100 us), one ahead keeps the GPU busy.
+        const int lag = vec_bytes(P, 20) > 6e8 ? 0 : 2;
         int it = 0;
         std::vector<RhsState> init = read_states(sin());
         bool any_run = false;
@@ -500,7 +510,7 @@ class EoCore : public EoMem {
                 poll_here = true;
             } else {
                 poll_here = ((it + 1) % poll_every == 0) || it + 1 == maxiter;
-                iterate(x, poll_here ? mirror_dev(slot) : nullptr);
+                iterate(x, poll_here ? mirror_dev(slot) : nullptr, it == 0 && !resume);
                 it++;
             }
             if (!poll_here) continue;
@@ -578,8 +588,8 @@ class EoCore : public EoMem {
         }
     }
 
-    void iterate(Spinor x, RhsState *mir) {
-        if (method == WILSON_SOLVER_BICGSTAB_EO) bicg_iter(x, mir);
+    void iterate(Spinor x, RhsState *mir, bool first = false) {
+        if (method == WILSON_SOLVER_BICGSTAB_EO) bicg_iter(x, mir, first);
         else if (method == WILSON_SOLVER_BLOCK_BICGSTAB_EO) block_iter(x, mir);
         else cg_iter(x, mir);
     }
@@ -638,10 +648,11 @@ class EoCore : public EoMem {
         ctx->flops_issued += c->flops;
     }
 
-    void bicg_iter(Spinor x, RhsState *mir) {
+    // first: the recurrence's first iteration, whose search direction start_fields has set
+    void bicg_iter(Spinor x, RhsState *mir, bool first = false) {
         const int nb = blas_nblocks(g, P);
         Spinor none;
-        {   // p = r + beta (p - omega v)
+        if (!first) {  // p = r + beta (p - omega v)
             BlasArgs a = blas_args(sin(), PH_RUN);
             a.a = p.f; a.b = r.f; a.c = v.f;
             run_blas(BL_P_UPDATE, a, vec_bytes(P, 4));
@@ -800,30 +811,27 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
     C.kappa.assign(C.nrhs, 0.0);
     std::copy(kappa, kappa + nrhs, C.kappa.begin());
 
-    // b -> parity fields; |b|^2
-    WL_HIP(launch_split(C.b_e.f, C.b_o.f, b_canon, g, nrhs, ctx->stream));
-    {
-        std::vector<RhsState> h(nrhs);
-        std::memset(h.data(), 0, sizeof(RhsState) * nrhs);
-        for (auto &s : h) s.phase = PH_RUN;
-        C.upload_states(C.sout(), h);
-    }
-    C.norm2_full(C.b_e.f, C.b_o.f, C.sout());
-    std::vector<RhsState> hs = C.read_states(C.sout());
-    std::vector<double> bn2(nrhs), stop2(nrhs);
-    std::vector<int> status(nrhs, WILSON_NOT_CONVERGED), iters(nrhs, 0), cycles(nrhs, 0), restarts(nrhs, 0);
-    std::vector<char> done(nrhs, 0);
-    for (int k = 0; k < nrhs; k++) {
-        bn2[k] = hs[k].aux;
-        if (!std::isfinite(bn2[k])) throw Error(WILSON_NONFINITE, "right-hand side contains NaN or Inf");
-        stop2[k] = tol[k] * tol[k] * bn2[k];
-    }
+    // b -> parity fields, |b|^2; x_0; b'.  Without an initial guess the first even residual is
+    // b' - M 0 = b' itself: a mixed solve takes it, and its norm from that hop's epilogue.
+    const bool first_is_bp = C.mixed && !prm.use_x0;
+    C.set_states(C.salt(), PH_RUN);
+    C.set_states(C.sout(), PH_RUN);
+    C.take_rhs(b_canon, C.salt());
     if (prm.use_x0) {
         WL_HIP(launch_split_one(C.x_e.f, x_canon, g, 0, nrhs, ctx->stream));
     } else {
         WL_HIP(launch_zero(C.x_e.f, g, nrhs, ctx->stream));
     }
-    C.prepare_bprime();
+    C.prepare_bprime(first_is_bp ? C.sout() : nullptr);
+    if (C.mixed && prm.use_x0) C.outer_residual();
+    std::vector<double> bn2, rr2, stop2(nrhs);  // rr2: |first even residual|^2 (mixed)
+    C.read_aux(C.salt(), C.sout(), bn2, rr2);
+    std::vector<int> status(nrhs, WILSON_NOT_CONVERGED), iters(nrhs, 0), cycles(nrhs, 0), restarts(nrhs, 0);
+    std::vector<char> done(nrhs, 0);
+    for (int k = 0; k < nrhs; k++) {
+        if (!std::isfinite(bn2[k])) throw Error(WILSON_NONFINITE, "right-hand side contains NaN or Inf");
+        stop2[k] = tol[k] * tol[k] * bn2[k];
+    }
     int used = 0;  // inner iterations consumed (max over RHS: they run in lockstep)
     std::vector<double> res2(nrhs, 0.0);
     bool checked = false;
@@ -953,18 +961,15 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
         // fields are not rescaled between cycles (FP32 and per-site-scaled FP16 keep the
         // range of a 1e-10 relative residual).
         const double delta = prm.inner_tol > 0 ? prm.inner_tol : (C.P == P32 ? 1e-5 : 1e-2);
-        C.outer_residual();
-        std::vector<RhsState> h = C.read_states(C.sout());
-        std::vector<double> prev(nrhs, 0.0), inner_stop(nrhs, 0.0);
+        std::vector<double> prev = rr2, inner_stop(nrhs, 0.0);
         std::vector<int> stall(nrhs, 0);
-        for (int k = 0; k < nrhs; k++) prev[k] = h[k].aux;
         std::vector<RhsState> rec;  // the recurrence to resume (empty: start one)
         const int max_cycles = 400;
         for (int cyc = 0; cyc < max_cycles; cyc++) {
             std::vector<char> active(nrhs);
             for (int k = 0; k < nrhs; k++) {
                 if (done[k]) { active[k] = 0; continue; }
-                const double rr = h[k].aux;
+                const double rr = rr2[k];
                 if (!std::isfinite(rr)) { status[k] = WILSON_NONFINITE; done[k] = 1; active[k] = 0; continue; }
                 if (rr <= stop2[k]) { done[k] = 2; active[k] = 0; continue; }  // confirmed below
                 active[k] = 1;
@@ -981,14 +986,15 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
             WL_HIP(launch_zero(C.xin.f, g, nrhs, ctx->stream));
             std::vector<RhsState> fin;
             if (fresh) {
-                WL_HIP(launch_convert(C.rf.f, C.r64.f, g, nrhs, C.sout(), 0, ctx->stream));
+                const Spinor res = first_is_bp && cyc == 0 ? C.bp.f : C.r64.f;
+                WL_HIP(launch_convert(C.rf.f, res, g, nrhs, C.sout(), 0, ctx->stream));
                 fin = C.inner_solve(C.rf.f, C.xin.f, false, active, inner_stop, budget, prm.poll_every);
             } else {
                 WL_HIP(launch_convert(C.r.f, C.r64.f, g, nrhs, C.sout(), 0, ctx->stream));  // r <- true residual
                 for (int k = 0; k < nrhs; k++) {
                     rec[k].phase = active[k] ? PH_RUN : PH_IDLE;
                     rec[k].stop2 = inner_stop[k];
-                    rec[k].r2 = h[k].aux;
+                    rec[k].r2 = rr2[k];
                     rec[k].iter = 0;
                     rec[k].fail = FAIL_NONE;
                 }
@@ -1009,13 +1015,14 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
             used += std::max(mx, 1);
             WL_HIP(launch_axpy_f64(C.x_e.f, C.xin.f, g, nrhs, C.sout(), 0, ctx->stream));
             C.outer_residual();
-            h = C.read_states(C.sout());
+            const std::vector<RhsState> h = C.read_states(C.sout());
             for (int k = 0; k < nrhs; k++) {
+                rr2[k] = h[k].aux;
                 if (!active[k] || done[k]) continue;
                 // no progress over 8 cycles in a row: give up
-                stall[k] = h[k].aux > 0.9 * prev[k] ? stall[k] + 1 : 0;
+                stall[k] = rr2[k] > 0.9 * prev[k] ? stall[k] + 1 : 0;
                 if (stall[k] >= 8) { status[k] = WILSON_NOT_CONVERGED; done[k] = 1; }
-                prev[k] = h[k].aux;
+                prev[k] = rr2[k];
             }
         }
         true_check();
@@ -1028,17 +1035,14 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
         // FP64 defect correction on the even system around low-precision inner solves
         const double delta = prm.inner_tol > 0 ? prm.inner_tol : (C.P == P32 ? 1e-5 : 1e-2);
         std::vector<double> inner_stop(nrhs, delta * delta);  // inner rhs has unit norm
-        std::vector<double> prev(nrhs, 0.0);
+        std::vector<double> prev = rr2;
         std::vector<int> stall(nrhs, 0);
-        C.outer_residual();
-        std::vector<RhsState> h = C.read_states(C.sout());
-        for (int k = 0; k < nrhs; k++) prev[k] = h[k].aux;
         const int max_cycles = 200;
         for (int cyc = 0; cyc < max_cycles; cyc++) {
             std::vector<char> active(nrhs);
             for (int k = 0; k < nrhs; k++) {
                 if (done[k]) { active[k] = 0; continue; }
-                const double rr = h[k].aux;
+                const double rr = rr2[k];
                 if (!std::isfinite(rr)) { status[k] = WILSON_NONFINITE; done[k] = 1; active[k] = 0; continue; }
                 if (rr <= stop2[k]) { done[k] = 2; active[k] = 0; continue; }  // candidate, confirmed below
                 active[k] = 1;
@@ -1046,7 +1050,8 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
             if (std::none_of(active.begin(), active.end(), [](char c) { return c; })) break;
             const int budget = prm.maxiter - used;
             if (budget <= 0) break;
-            WL_HIP(launch_convert(C.rf.f, C.r64.f, g, nrhs, C.sout(), 1, ctx->stream));
+            const Spinor res = first_is_bp && cyc == 0 ? C.bp.f : C.r64.f;
+            WL_HIP(launch_convert(C.rf.f, res, g, nrhs, C.sout(), 1, ctx->stream));
             WL_HIP(launch_zero(C.xin.f, g, nrhs, ctx->stream));
             std::vector<RhsState> fin = C.inner_solve(C.rf.f, C.xin.f, false, active, inner_stop, budget,
                                                       prm.poll_every);
@@ -1060,12 +1065,13 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
             used += std::max(mx, 1);
             WL_HIP(launch_axpy_f64(C.x_e.f, C.xin.f, g, nrhs, C.sout(), 1, ctx->stream));
             C.outer_residual();
-            h = C.read_states(C.sout());
+            const std::vector<RhsState> h = C.read_states(C.sout());
             for (int k = 0; k < nrhs; k++) {
+                rr2[k] = h[k].aux;
                 if (!active[k]) continue;
-                if (h[k].aux > 0.25 * prev[k]) stall[k]++;
+                if (rr2[k] > 0.25 * prev[k]) stall[k]++;
                 if (stall[k] >= 4) { status[k] = WILSON_NOT_CONVERGED; done[k] = 1; }
-                prev[k] = h[k].aux;
+                prev[k] = rr2[k];
             }
         }
         true_check();
@@ -1237,39 +1243,22 @@ class BatchEngine {
         C->prefin = prefin_enabled();
         C->kappa.assign(nslots, 0.0);
         delta = p.inner_tol > 0 ? p.inner_tol : (C->P == P32 ? 1e-5 : (C->P == P16 ? 1e-2 : 0.0));
-        std::vector<RhsState> h(n);
-        std::memset(h.data(), 0, sizeof(RhsState) * n);
-        for (auto &s : h) s.phase = PH_IDLE;
         C->select_all();
-        C->upload_states(C->sin(), h);
-        C->upload_states(C->sout(), h);
+        for (RhsState *st : {C->sin(), C->sout(), C->salt()}) C->set_states(st, PH_IDLE);
         WL_HIP(hipStreamSynchronize(ctx->stream));
     }
 
     // start a Krylov cycle for slot k on rhs (inner precision) and solution x
     void start_inner(int k, Spinor rhs, Spinor x, bool use_x0, double stop2) {
         C->select(k, 1);
-        std::vector<RhsState> h(1);
-        std::memset(h.data(), 0, sizeof(RhsState));
-        h[0].phase = PH_RUN;
-        h[0].stop2 = stop2;
-        C->upload_states(C->sin(), h);
+        C->set_states(C->sin(), PH_RUN, nullptr, &stop2);
         const int nb = blas_nblocks(C->g, C->P);
         Spinor none;
         if (C->method == WILSON_SOLVER_BICGSTAB_EO) {
-            BlasArgs a = C->blas_args(C->sin(), PH_RUN);
-            if (use_x0) {
-                C->apply_M(C->r.f, x, C->tmp.f, false, RED_NONE, none, C->sin(), PH_RUN, &rhs);
-                a.a = C->rh.f; a.b = C->r.f;
-                C->run_blas(BL_COPY_NORM, a, 0);
-            } else {
-                a.a = C->r.f; a.b = rhs;
-                C->run_blas(BL_COPY_NORM, a, 0);
-                a.a = C->rh.f; a.b = rhs;
-                C->run_blas(BL_COPY_NORM, a, 0);
-            }
+            C->start_fields(use_x0, x, rhs);
             C->finalize(FIN_BICG_INIT, 1, nb, C->sin(), PH_RUN);
-            for (Spinor f : {C->p.f, C->v.f, C->t.f}) WL_HIP(launch_zero(C->V(f), C->g, 1, ctx->stream));
+            // (this slot's first iteration runs with the others' p update, at beta = 0)
+            WL_HIP(launch_zero(C->V(C->v.f), C->g, 1, ctx->stream));
         } else {
             if (use_x0) {
                 const int hb = C->apply_M(C->r.f, x, C->tmp.f, false, RED_NORM2, none, C->sin(), PH_RUN, &rhs);
@@ -1289,10 +1278,12 @@ class BatchEngine {
         C->select_all();
     }
 
-    void begin_cycle(int k) {
+    // first: the residual is b' itself (x = 0)
+    void begin_cycle(int k, bool first = false) {
         if (C->mixed) {
             C->select(k, 1);
-            WL_HIP(launch_convert(C->V(C->rf.f), C->V(C->r64.f), C->g, 1, C->S(C->sout()), 1, ctx->stream));
+            WL_HIP(launch_convert(C->V(C->rf.f), C->V(first ? C->bp.f : C->r64.f), C->g, 1, C->S(C->sout()), 1,
+                                  ctx->stream));
             WL_HIP(launch_zero(C->V(C->xin.f), C->g, 1, ctx->stream));
             C->select_all();
             start_inner(k, C->rf.f, C->xin.f, false, delta * delta);
@@ -1317,10 +1308,7 @@ class BatchEngine {
         s.state = FINISHED;
         s.ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - s.t0).count();
         C->select(k, 1);
-        std::vector<RhsState> h(1);
-        std::memset(h.data(), 0, sizeof(RhsState));
-        h[0].phase = PH_IDLE;
-        C->upload_states(C->sin(), h);
+        C->set_states(C->sin(), PH_IDLE);
         C->select_all();
     }
 
@@ -1335,10 +1323,13 @@ class BatchEngine {
         s.t0 = std::chrono::steady_clock::now();
         C->kappa[k] = kappa;
         C->select(k, 1);
-        WL_HIP(launch_split(C->V(C->b_e.f), C->V(C->b_o.f), b_dev, C->g, 1, ctx->stream));
-        C->norm2_full(C->b_e.f, C->b_o.f, C->sout());
-        s.bn2 = C->read_states(C->sout())[0].aux;
+        C->take_rhs(b_dev, C->salt());
+        WL_HIP(launch_zero(C->V(C->x_e.f), C->g, 1, ctx->stream));
+        C->prepare_bprime(C->mixed ? C->sout() : nullptr);
+        std::vector<double> bn2, rr2;
+        C->read_aux(C->salt(), C->sout(), bn2, rr2);
         C->select_all();
+        s.bn2 = bn2[0];
         if (!std::isfinite(s.bn2)) {
             s.state = FINISHED;
             s.status = WILSON_NONFINITE;
@@ -1346,14 +1337,7 @@ class BatchEngine {
         }
         s.stop2 = tol * tol * s.bn2;
         s.state = RUNNING;
-        C->select(k, 1);
-        WL_HIP(launch_zero(C->V(C->x_e.f), C->g, 1, ctx->stream));
-        C->prepare_bprime();
-        if (C->mixed) {
-            C->outer_residual();
-            s.prev = C->read_states(C->sout())[0].aux;
-        }
-        C->select_all();
+        s.prev = rr2[0];
         if (s.bn2 == 0.0) {
             C->select(k, 1);
             C->reconstruct();
@@ -1362,7 +1346,7 @@ class BatchEngine {
             finish(k, WILSON_OK);
             return WILSON_OK;
         }
-        begin_cycle(k);
+        begin_cycle(k, true);
         return WILSON_OK;
     }
 
