@@ -227,7 +227,7 @@ struct FullArgs {
     Geom g;
     int par;
     int nrhs;
-    Spinor f[2];         // full kernel: the input's parity planes
+    Spinor f[2];         // full and rhs kernels: the input's parity planes
     const double2 *in;   // small kernel: the canonical input
     const void *gauge;
     int gprec, recon;
@@ -240,6 +240,8 @@ inline int full_zblk(const Geom &g) {
 }
 hipError_t launch_dslash_full(const FullArgs &p, hipStream_t s);
 hipError_t launch_dslash_small(const FullArgs &p, int sp, hipStream_t s);
+// one parity of every right-hand side from the planes p.f[1 - par] (and + p.f[par] with has_y)
+hipError_t launch_dslash_rhs(const FullArgs &p, int par, int has_y, hipStream_t s);
 
 // A finalize run at the start of a vector kernel instead of a launch of its own (short
 // partial rows only): the scalar step `op` on the `nv` values of each right-hand side's

@@ -8,8 +8,11 @@
 // other parity's stencil is centred on, come from the caches, and a block's result leaves
 // as whole canonical rows through LDS.
 //
-// Two kernels:
+// Three kernels:
 //   dslash_full_kernel   from parity planes (large lattices: bound by HBM);
+//   dslash_rhs_kernel    one parity of several right-hand sides from parity planes, the
+//                        result written to the canonical layout by the wave that has it
+//                        instead of to planes that another pass reads back;
 //   dslash_small_kernel  from the canonical input itself, five waves per 64 output sites as
 //                        in the solvers' direction split (lattices whose fields fit the
 //                        caches: the call is bound by launches and latency, and one launch
@@ -94,6 +97,74 @@ dslash_full_kernel(const FullArgs p, const VisitOrder vo) {
             d.x = (double)x.re;
             d.y = (double)x.im;
             __builtin_nontemporal_store(d, gptr_w(dst) + e);
+        }
+    }
+}
+
+// One parity of nrhs right-hand sides.  With LL the waves of a block take successive right-hand
+// sides of the same 64 sites and share the tile's links through LDS (as the tuned hops of 12
+// right-hand sides do); without, a block takes 256 sites of one.  Each wave then turns its 64
+// results in LDS (the links' room, one padded row per site) and writes their 192-byte chunks
+// five and a third per access.  Bound by the plane loads' requests and the canonical writes: 24^3x48,
+// 12 RHS in FP32, one parity 400 us where the hop and the conversion of its result took 497
+// (1.15 GB moved at the least).
+template <int SP, int GP, int NE, bool SHX, bool LL>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HopOcc<SP, 1>::value)))
+dslash_rhs_kernel(const FullArgs p, int par, int has_y, const VisitOrder vo) {
+    using R = real_t<SP>;
+    extern __shared__ __align__(16) char rhs_lds[];
+    const Geom &g = p.g;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+    const int lb = xcd_tile(blockIdx.x, gridDim.x), groups = LL ? p.nrhs / ((int)blockDim.x >> 6) : p.nrhs;
+    const int tile = lb / groups, grp = lb - tile * groups;
+    const int rhs = LL ? grp * ((int)blockDim.x >> 6) + w : grp;
+    const int l = LL ? tile * 64 + lane : tile * 256 + (int)threadIdx.x;
+    const bool valid = l < g.Vh;
+    const int i = valid ? visit_order(l, g, vo) : g.Vh - 1;
+    const SiteXY c = cb_coords(g, i, par);
+    const SiteNbrs nb = site_nbrs(g, i, c);
+    const Spinor fp = par ? p.f[1] : p.f[0];
+    const HopSource a = {par ? p.f[0] : p.f[1], p.gauge};
+    const bool act[1] = {true};
+    if constexpr (LL) {
+        const int lsite[8] = {i, nb.xm, i, nb.ym, i, nb.zm, i, nb.tm};
+        stage_links<GP, NE>(rhs_lds, a, par, lsite, g.stride);
+    }
+    Cx<R> acc[1][4][3];
+    hop_sum<SP, GP, 1, NE, false, false, SHX, LL, 0>(acc, a, g, par, i, c, nb, rhs, act, g.stride, rhs_lds);
+    // (complete here, as in dslash_full_kernel)
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) asm volatile("" : "+v"(acc[0][s][k].re), "+v"(acc[0][s][k].im));
+    const R cH = (R)p.cH;
+    Cx<R> o[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) o[k] = cscale(acc[0][k / 3][k % 3], cH);
+    if (has_y) {
+        Cx<R> y[12];
+        load_site<SP, R, true>(y, fp, g.stride, rhs, i);
+#pragma unroll
+        for (int k = 0; k < 12; k++) o[k] = cadd(o[k], y[k]);
+    }
+    as_stored<SP, R>(o);
+    if constexpr (LL) __syncthreads();  // every wave has read the links
+    Cx<R> *row = reinterpret_cast<Cx<R> *>(rhs_lds) + w * 64 * kCanonRow;
+#pragma unroll
+    for (int k = 0; k < 12; k++) row[lane * kCanonRow + k] = o[k];
+    __syncthreads();
+    const int s = valid ? 2 * i + c.b : -1;
+    dvec2 *dst = reinterpret_cast<dvec2 *>(p.out) + (size_t)rhs * g.Vh * 24;
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        const int e = k * 64 + lane, o_ = e / 12;
+        const int so = __shfl(s, o_, 64);
+        if (so >= 0) {
+            const Cx<R> x = row[o_ * kCanonRow + (e - o_ * 12)];
+            dvec2 d;
+            d.x = (double)x.re;
+            d.y = (double)x.im;
+            __builtin_nontemporal_store(d, gptr_w(dst) + ((size_t)so * 12 + (e - o_ * 12)));
         }
     }
 }
@@ -232,6 +303,44 @@ static hipError_t small_pg(const FullArgs &p, hipStream_t s) {
     if (p.recon == 12) hipLaunchKernelGGL((dslash_small_kernel<SP, GP, 6>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((dslash_small_kernel<SP, GP, 9>), grid, block, 0, s, p);
     return hipGetLastError();
+}
+
+template <int SP, int GP, int NE>
+static hipError_t rhs_pgn(const FullArgs &p, int par, int has_y, hipStream_t s) {
+    constexpr bool SHX = SP != P64;
+    constexpr size_t turn = 64 * kCanonRow * 2 * sizeof(real_t<SP>);  // one wave's
+    // t visited inside eighths of z (24^3x48, 12 RHS in FP32: 606 us, against 619 for quarters, 626 for
+    // twelfths and 630 in plain order)
+    const int zblk = p.g.L[2] % 8 == 0 && (p.g.Lxh * p.g.L[1]) % 64 == 0 ? p.g.L[2] / 8 : 0;
+    // Links in LDS for 4 or 3 right-hand sides at a time: at 24^3x48 one parity of 12 takes 631 us
+    // against 687 without in FP32 and 881 against 954 in FP64, with the conversion.  Two at a time do
+    // not repay the barriers (109 against 103 us in FP32), nor do FP16's short loads (569 against
+    // 566); whole links (18 reals) take the registers or the LDS (FP32 1141 against 746).
+    if constexpr (SP != P16 && NE == 6) {
+        const int nw = p.nrhs % 4 == 0 ? 4 : (p.nrhs % 3 == 0 ? 3 : 1);
+        if (nw > 1) {
+            constexpr size_t links = 8 * LinkElems<GP, NE>::N * 64 * LinkPack<GP>::EB;
+            const size_t lds = nw * turn > links ? nw * turn : links;
+            const dim3 grid((p.g.Vh + 63) / 64 * (p.nrhs / nw)), block(64 * nw);
+            hipLaunchKernelGGL((dslash_rhs_kernel<SP, GP, NE, SHX, true>), grid, block, lds, s, p, par, has_y,
+                               make_visit_order(p.g, zblk));
+            return hipGetLastError();
+        }
+    }
+    const dim3 grid((p.g.Vh + 255) / 256 * p.nrhs), block(256);
+    hipLaunchKernelGGL((dslash_rhs_kernel<SP, GP, NE, SHX, false>), grid, block, 4 * turn, s, p, par, has_y,
+                       make_visit_order(p.g, zblk));
+    return hipGetLastError();
+}
+hipError_t launch_dslash_rhs(const FullArgs &p, int par, int has_y, hipStream_t s) {
+    const int sp = p.f[1 - par].prec, gp = p.gprec;
+    if ((p.recon != 12 && p.recon != 18) || p.nrhs < 1 || p.nrhs > kMaxRhs || par < 0 || par > 1) return hipErrorInvalidValue;
+    const bool two = p.recon == 12;
+    if (sp == P64 && gp == P64) return two ? rhs_pgn<P64, P64, 6>(p, par, has_y, s) : rhs_pgn<P64, P64, 9>(p, par, has_y, s);
+    if (sp == P32 && gp == P32) return two ? rhs_pgn<P32, P32, 6>(p, par, has_y, s) : rhs_pgn<P32, P32, 9>(p, par, has_y, s);
+    if (sp == P16 && gp == P16) return two ? rhs_pgn<P16, P16, 6>(p, par, has_y, s) : rhs_pgn<P16, P16, 9>(p, par, has_y, s);
+    if (sp == P16 && gp == P32) return two ? rhs_pgn<P16, P32, 6>(p, par, has_y, s) : rhs_pgn<P16, P32, 9>(p, par, has_y, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_dslash_full(const FullArgs &p, hipStream_t s) {

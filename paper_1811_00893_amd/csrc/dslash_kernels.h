@@ -353,8 +353,8 @@ __device__ __forceinline__ void hop_finish(const HopArgs &a, int i, bool valid, 
 // tile is needed by every wave: the waves load it once into LDS, wave w the directions
 // d = w, w + nw, ... (lane l for site l of the tile), and everyone reads it from there.
 // Every wave of the block calls this (it holds a block barrier).
-template <int GP, int NE>
-__device__ __forceinline__ void stage_links(char *ll, const HopArgs &a, int par, const int (&lsite)[8], int stride) {
+template <int GP, int NE, typename A>
+__device__ __forceinline__ void stage_links(char *ll, const A &a, int par, const int (&lsite)[8], int stride) {
     constexpr int NL = LinkElems<GP, NE>::N;
     constexpr unsigned EB = LinkPack<GP>::EB;
     const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6, nw = (int)blockDim.x >> 6;

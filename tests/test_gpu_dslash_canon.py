@@ -100,3 +100,40 @@ def test_plain_calls_in_turn(L):
         x = torch.zeros_like(psi, device=DEV)
         assert L.wilson_solve(x, psi.to(DEV), U.to(DEV), 0.11, dims, 1e-10, 1000) == 0
         assert rel(oracle.apply_D(x.cpu().numpy(), U.numpy(), 0.11, dims), psi.numpy()) < 1e-10
+
+
+# FP64 takes the plane kernels at (18, 10, 14, 22) (27720 sites per parity, ragged in tiles of 64
+# and 256) for 5 or 6 right-hand sides, FP32 and FP16 at both sizes for any number; 4, 3 and 6 share
+# links in blocks of four and three waves (FP64, FP32), 2 and 5 do not.
+@pytest.mark.parametrize("dims,nrhs", [((8, 8, 8, 16), 2), ((8, 8, 8, 16), 4), ((18, 10, 14, 22), 3),
+                                       ((18, 10, 14, 22), 5), ((18, 10, 14, 22), 6)])
+@pytest.mark.parametrize("scale", [1.0, 1.25])
+def test_several_rhs_match_oracle_and_the_timed_path(L, dims, nrhs, scale):
+    """Hops that write the canonical layout; with per-launch timing the call goes through the
+    solvers' hop, whose FP32 and FP16 results are the same to the bit."""
+    U = scale * inputs.gauge_field(dims, eps=0.3, seed=4110)
+    psi = inputs.gaussian_source(dims, seed=4111, nrhs=nrhs)
+    prev = inputs.gaussian_source(dims, seed=4112, nrhs=nrhs)
+    on = {0: oracle.parity_of_sites(dims) == 0, 1: oracle.parity_of_sites(dims) == 1, 2: np.ones(psi.shape[1], bool)}
+    ctx = L.wilson_context_create()
+    g = L.wilson_gauge_load(ctx, U.to(DEV), dims, L.WILSON_GAUGE_FP32 | L.WILSON_GAUGE_FP16)
+    try:
+        for parity in (2, 0, 1):
+            ref = np.stack([oracle.dslash(psi.numpy()[k], U.numpy(), 0.124, dims, parity, out=prev.numpy()[k])
+                            for k in range(nrhs)])
+            for prec in (0, 1, 2, 3) if scale == 1.0 else (0, 1):
+                got = []
+                for timed in (False, True):
+                    out = prev.to(DEV).clone()
+                    L.wilson_timing_enable(ctx, timed)
+                    L.check(L.wilson_dslash_ex(ctx, g, out, psi.to(DEV), 0.124, parity, prec, nrhs), "dslash")
+                    L.wilson_timing_enable(ctx, False)
+                    torch.cuda.synchronize()
+                    got.append(out.cpu().numpy())
+                for k in range(nrhs):
+                    assert rel(got[0][k][on[parity]], ref[k][on[parity]]) < LIMIT[prec], (parity, prec, k)
+                assert np.array_equal(got[0][:, ~on[parity]], prev.numpy()[:, ~on[parity]]), (parity, prec)
+                assert prec == 0 or np.array_equal(got[0], got[1]), (parity, prec)
+    finally:
+        L.wilson_gauge_free(ctx, g)
+        L.wilson_context_destroy(ctx)
