@@ -172,7 +172,9 @@ typedef struct {
  *                  allowed.
  *   parity 2:      out = D * in = in - kappa * H * in on every site; out == in is rejected.
  * out, in: 12*V complex each.  U: 36*V complex (periodic links).  kappa finite.
- * Uses an internal context on the default stream; synchronous.
+ * Uses an internal context on the default stream; synchronous.  Its link buffer (up to 512 MiB,
+ * one lattice shape and device at a time; the contents are packed from U on every call) stays
+ * allocated for the next plain call and is given back when an allocation fails.
  */
 int wilson_dslash(double *out, const double *in, const double *U, double kappa, const int32_t dims[4],
                   int32_t parity);

@@ -49,6 +49,9 @@ constexpr int kCanonRow = 13;  // padded LDS row of one site: 12 complex and one
 // A block holds 128 checkerboard sites of each parity (waves 0, 1 even, 2, 3 odd): the 256
 // consecutive canonical sites 2 i0 .. 2 i0 + 255, since checkerboard site i of either parity
 // is one of the full sites 2i, 2i + 1.
+// Bound by the plane loads, as the hop, and by the canonical rows it writes: 32^3x64 FP64, D takes
+// 626 us (142 split + 472 here) against 944 as two conversions each way and two hops of 278;
+// what it must move (input, output, links once) is 2.0 GB, 305 us at a copy's 6.6 TB/s.
 template <int SP, int GP, int NE, bool SHX>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HopOcc<SP, 1>::value)))
 dslash_full_kernel(const FullArgs p, const VisitOrder vo) {
@@ -222,7 +225,8 @@ __device__ __forceinline__ void small_dir(Cx<real_t<SP>> (&acc)[1][4][3], const 
 
 // p.par = 0 or 1: the parity hop alone (out = cH H in on that parity's sites); 2: D on both.
 // blockIdx.x = (tile * parities + parity) * nrhs + rhs.  The four directions are added in
-// the order of the solvers' direction split.
+// the order of the solvers' direction split.  Bound by latency: D at 8^4 in FP64 6.4 us against
+// 24.6 in six launches.
 template <int SP, int GP, int NE>
 __global__ void __launch_bounds__(320) dslash_small_kernel(const FullArgs p) {
     using R = real_t<SP>;

