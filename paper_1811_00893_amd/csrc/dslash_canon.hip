@@ -51,7 +51,7 @@ constexpr int kCanonRow = 13;  // padded LDS row of one site: 12 complex and one
 // is one of the full sites 2i, 2i + 1.
 // Bound by the plane loads, as the hop, and by the canonical rows it writes: 32^3x64 FP64, D takes
 // 626 us (142 split + 472 here) against 944 as two conversions each way and two hops of 278;
-// what it must move (input, output, links once) is 2.0 GB, 305 us at a copy's 6.6 TB/s.
+// what it must move (input, output, links once) is 1.6 GB, 244 us at a copy's 6.6 TB/s.
 template <int SP, int GP, int NE, bool SHX>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HopOcc<SP, 1>::value)))
 dslash_full_kernel(const FullArgs p, const VisitOrder vo) {
