@@ -487,9 +487,13 @@ class EoCore : public EoMem {
         }
         // Enqueue iterations ahead of the host, which polls `lag` iterations behind the newest but
         // one.  The iterations in flight when the solve converges run masked, but still launch
-        // (11 kernels, 5-25 us each with the lattice's blocks): where an iteration takes longer
-        // than the host needs to enqueue one (~100 us), one ahead keeps the GPU busy.
-        const int lag = vec_bytes(P, 20) > 6e8 ? 0 : 2;
+        // (11 kernels, 5-25 us each with the lattice's blocks); with none behind, the GPU waits a few us
+        // for the host after each iteration.  Whole solves, ms, lag 0 / 1 / 2, by the bytes of 20
+        // vectors: CGNR 20x12x28x36 FP64 (0.46 GB) 12.5 / 12.1 / 12.1, clover 24^3x48 FP32 inner
+        // (0.64) 12.18 / 11.96 / 12.04, 32^3x64 FP64 (4.0) 41.3 / 41.2 / 41.25, 24^3x48 FP32 inner with
+        // 12 RHS (7.6) 62.8 / 63.0 / 63.5.
+        const double size = vec_bytes(P, 20);
+        const int lag = size > 6e9 ? 0 : (size > 6e8 ? 1 : 2);
         int it = 0;
         std::vector<RhsState> init = read_states(sin());
         bool any_run = false;
