@@ -1187,32 +1187,29 @@ void dslash_device(wilson_ctx *ctx, const wilson_gauge *G, double *out, const do
         run_own(np, [&]() { return launch_dslash_small(f, P, ctx->stream); });
         return;
     }
-    if (own && parity == 2 && nrhs == 1) {
-        f.f[0] = ws->in[0].f;
-        f.f[1] = ws->in[1].f;
-        WL_HIP(launch_split(f.f[0], f.f[1], in, g, nrhs, ctx->stream));
-        run_own(2, [&]() { return launch_dslash_full(f, ctx->stream); });
-        return;
-    }
     if (parity == 2) WL_HIP(launch_split(ws->in[0].f, ws->in[1].f, in, g, nrhs, ctx->stream));
     else WL_HIP(launch_split_one(ws->in[1 - parity].f, in, g, 1 - parity, nrhs, ctx->stream));
-    // Several right-hand sides: hops that write the canonical layout themselves (one parity of 12
-    // FP32 RHS at 24^3x48: 628 us against 727 through the hop's planes).  Under per-launch timing the
-    // solvers' hop runs between the conversions, as it is what the hop class times; and FP32 and
-    // FP16 fields keep to it where its tuned shape adds the directions in another order (as for
-    // the small kernel).
+    // D on one right-hand side in one launch, and hops of several that write the canonical layout
+    // themselves (one parity of 12 FP32 RHS at 24^3x48: 628 us against 727 through the hop's
+    // planes).  FP32 and FP16 fields keep to the hop where its tuned shape adds the directions in
+    // another order (as for the small kernel).  Under per-launch timing the solvers' hop of
+    // several right-hand sides runs between the conversions, as it is what the hop class times.
     a.par = parity == 2 ? 0 : parity;
     a.out = ws->out[a.par].f;
     a.in = ws->in[1 - a.par].f;
     if (parity == 2) a.y = ws->in[0].f;
-    bool rows = own && nrhs > 1 && !ctx->timing;
-    if (rows && P != P64) {
+    bool canon = own && (nrhs == 1 ? parity == 2 : !ctx->timing);
+    if (canon && P != P64) {
         const LaunchCfg c = hop_config(ctx, a);
-        rows = !c.dsplit && !c.tm;
+        canon = !c.dsplit && !c.tm;
     }
-    if (rows) {
+    if (canon) {
         f.f[0] = ws->in[0].f;
         f.f[1] = ws->in[1].f;
+        if (nrhs == 1) {
+            run_own(2, [&]() { return launch_dslash_full(f, ctx->stream); });
+            return;
+        }
         for (int par = 0; par < 2; par++)
             if (parity == 2 || parity == par)
                 run_own(1, [&]() { return launch_dslash_rhs(f, par, parity == 2, ctx->stream); });
