@@ -53,6 +53,11 @@
  *   WILSON_RECON=18        keep all 18 reals of every link (default: the first two rows
  *                          when every link is SU(3) to 1e-13, the third rebuilt in the
  *                          kernels).
+ *   WILSON_ONE_LAUNCH=n    BiCGStab on small lattices runs in one launch whose blocks wait for
+ *                          each other; a block gives up after n polls of a wait (default
+ *                          2^21, a second or two) and the solve starts again in separate
+ *                          launches, with the same results bit for bit, as does every later
+ *                          one of the context (0: separate launches at once).
  *   WILSON_GRAPHS=1        on lattices up to 2^16 sites per parity, replay solver
  *                          iterations in chunks of four from captured HIP graphs (same
  *                          results bit for bit; measured slower than direct launches on

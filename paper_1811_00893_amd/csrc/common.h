@@ -79,7 +79,7 @@ inline size_t spinor_field_bytes(int prec, const Geom &g) {
 // Per-right-hand-side Krylov state, resident on the device.  The scalars of the
 // iteration are computed on the device, so the host never has to wait for them.
 enum Phase : int { PH_IDLE = 1, PH_RUN = 2, PH_SCONV = 4, PH_DONE = 8, PH_FAIL = 16 };
-enum FailCode : int { FAIL_NONE = 0, FAIL_BREAKDOWN = 1, FAIL_NONFINITE = 2, FAIL_DEVICE = 3 };
+enum FailCode : int { FAIL_NONE = 0, FAIL_BREAKDOWN = 1, FAIL_NONFINITE = 2 };
 
 constexpr int kStateRing = 4;  // host-mapped state mirrors of a solve in flight
 
@@ -97,7 +97,7 @@ struct alignas(16) RhsState {
     int phase;
     int fail;
     int iter;
-    int pad;
+    int lost;                   // a block of a one-launch solve gave up waiting (small_solve.hip)
 };
 
 // Reduction kinds a kernel epilogue can produce (values per block).
@@ -302,12 +302,15 @@ hipError_t launch_init_states(RhsState *st, const StateInit &init, hipStream_t s
 // BiCGStab iterations on M_ee in one cooperative launch (small lattices, no clover term): one
 // block per 64-site tile and right-hand side.  Fields hold nrhs right-hand sides; r, rhat and x
 // are set, p and v count as zero with `first`.  scratch: scratch_stride bytes per right-hand
-// side, the first 256 zero at the launch (barrier counter); state: phases, stop2 and scalars.
+// side, the first 256 zero at the launch (barrier counter); state: phases, stop2 and scalars,
+// `lost` zero.  A block that has polled a barrier more than `spins` times sets `lost` of its
+// right-hand side and ends; the others follow, and the fields and states are then worthless.
 struct SmallArgs {
     Geom g;
     int nrhs, tiles;
     int iters;           // at most this many iterations
     int first;
+    unsigned spins;
     const void *gauge;
     Spinor r, rh, p, v, s, x, tmp;
     char *scratch;

@@ -177,6 +177,7 @@ struct wilson_ctx {
     // the context, so those solves allocate nothing themselves)
     wl::SolveHostRes lend;
     int small_blocks[2][2] = {{-1, -1}, {-1, -1}};  // blocks of the one-launch solve the device holds (FP64 / FP32, 12 / 18 link reals)
+    bool small_lost = false;         // a one-launch solve was refused or gave up: this context takes the separate launches
     void *scratch = nullptr;         // device address of the no-allocation solve's array on this device
     hipStream_t capture_stream = nullptr;  // stream that iteration chunks are captured on (HIP graphs)
     bool no_tune = false;            // set for the duration of a call that must not tune

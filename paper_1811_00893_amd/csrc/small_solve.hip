@@ -15,7 +15,9 @@
 // between the XCDs' L2 caches without writing those back or invalidating them; a block's stores
 // have completed (s_waitcnt) before it arrives at a barrier, and it reads only after it has
 // seen every arrival.  The block's links are the same in every iteration and stay in registers.  The grid is launched cooperatively, so all its blocks are resident; a wait
-// is bounded all the same, and a block that gives up ends the solve with FAIL_DEVICE.
+// is bounded all the same, and a block that gives up marks the right-hand side as lost: the host
+// then runs the separate launches.  The mark has a word of its own, which no other store touches:
+// tile 0 may still see the last arrivals and store a state that looks finished.
 //
 // The arithmetic, the order of every sum and the scalar steps are those of the launches it
 // replaces (the direction-split hop, the element-wise vector kernels, the one-wave finalize),
@@ -48,7 +50,6 @@ __device__ __forceinline__ void dot(double (&red)[3], Cx<R> e, Cx<R> r) {  // |r
 namespace {
 
 constexpr int kWaves = 4;  // one per direction (one per SIMD, with all its registers); wave 0 finishes the hop
-constexpr unsigned kSpinLimit = 1u << 24;  // polls of a barrier before a block gives up (seconds)
 
 typedef unsigned long long u64;
 __device__ __forceinline__ void st_agent(void *p, u64 v) {
@@ -114,7 +115,7 @@ __device__ __forceinline__ void ld_shared_site(Cx<R> (&v)[12], BufRsrc f, int st
 
 // Barrier over the `tiles` blocks that share *cnt, the n-th: false if the wait gave up.  The
 // counter is compared modulo 2^32.
-__device__ __forceinline__ bool tiles_barrier(unsigned *cnt, unsigned n, int tiles, int *ok) {
+__device__ __forceinline__ bool tiles_barrier(unsigned *cnt, unsigned n, int tiles, unsigned spins, int *ok) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's exchanged stores are done
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -123,7 +124,7 @@ __device__ __forceinline__ bool tiles_barrier(unsigned *cnt, unsigned n, int til
         unsigned polls = 0;
         int good = 1;
         while ((int)(__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0)
-            if (++polls > kSpinLimit) {
+            if (++polls > spins) {
                 good = 0;
                 break;
             }
@@ -408,7 +409,7 @@ bicg_small_kernel(const SmallArgs p) {
                 for (int q = 0; q < EPW; q++)
                     if (lane == 0 && wv + kWaves * q < NEL) st_agent_d(sp + (wv + kWaves * q) * tiles + tile, red[q]);
             }
-            if (!(good = tiles_barrier(cnt, ++nbar, tiles, &ok))) break;
+            if (!(good = tiles_barrier(cnt, ++nbar, tiles, p.spins, &ok))) break;
             if (!first) {
                 step(FIN_BICG_S, 1, [&](int) { return blas_row(sp); });
                 if (!(loc.phase & PH_RUN)) break;  // |s| small enough: x += alpha p and stop
@@ -448,7 +449,7 @@ bicg_small_kernel(const SmallArgs p) {
                         if (lane < 3) st_agent_d(hp + lane * tiles + tile, lane == 0 ? rd[0] : (lane == 1 ? rd[1] : rd[2]));
                     }
                 });
-                if (!(good = tiles_barrier(cnt, ++nbar, tiles, &ok))) break;
+                if (!(good = tiles_barrier(cnt, ++nbar, tiles, p.spins, &ok))) break;
             }
             if (!good) break;
             if (first) own(v);
@@ -484,7 +485,7 @@ bicg_small_kernel(const SmallArgs p) {
                     if (lane == 0 && wv + kWaves * q < NEL)
                         st_agent_d(xp + (k * NEL + wv + kWaves * q) * tiles + tile, all[3 * q + k]);
         }
-        if (!(good = tiles_barrier(cnt, ++nbar, tiles, &ok))) break;
+        if (!(good = tiles_barrier(cnt, ++nbar, tiles, p.spins, &ok))) break;
         step(FIN_BICG_RHO, 3, [&](int k) { return blas_row(xp + k * NEL * tiles); });
         if (!(loc.phase & PH_RUN)) break;
     }
@@ -501,12 +502,17 @@ bicg_small_kernel(const SmallArgs p) {
             st_elem<SP, R>(const_cast<gchar *>(splane(p.v.data, rhs * NEL + e, stride)), off, v[q]);
         }
     }
-    if (threadIdx.x == 0 && (tile == 0 || !good)) {
+    if (threadIdx.x == 0) {
+        RhsState *st = &p.state[rhs];
         if (!good) {
-            loc.phase = PH_FAIL;
-            loc.fail = FAIL_DEVICE;
+            __hip_atomic_store(&st->lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else if (tile == 0) {  // every field but `lost`
+            static_assert(offsetof(RhsState, phase) == 14 * sizeof(double) && offsetof(RhsState, lost) == 14 * sizeof(double) + 12);
+            for (int k = 0; k < 14; k++) (&st->rho_re)[k] = (&loc.rho_re)[k];
+            st->phase = loc.phase;
+            st->fail = loc.fail;
+            st->iter = loc.iter;
         }
-        p.state[rhs] = loc;
     }
 }
 
@@ -544,11 +550,13 @@ hipError_t launch_bicg_small(const SmallArgs &p, int prec, int recon, hipStream_
     const void *k = small_kernel(prec, recon);
     const int nb = (prec == P64 ? 12 : 6) * ((p.g.Vh + 1023) / 1024);
     if (!k || p.tiles != (p.g.Vh + 63) / 64 || p.tiles > kPreFinMax || nb > kPreFinMax || p.nrhs < 1 || p.nrhs > kMaxRhs ||
-        p.iters < 1 || p.scratch_stride < small_scratch_bytes(p.g, prec))
+        p.iters < 1 || p.spins < 1 || p.scratch_stride < small_scratch_bytes(p.g, prec))
         return hipErrorInvalidValue;
     SmallArgs a = p;
     void *args[] = {&a};
-    return hipLaunchCooperativeKernel(k, dim3(p.tiles * p.nrhs), dim3(64 * kWaves), args, 0, s);
+    const hipError_t e = hipLaunchCooperativeKernel(k, dim3(p.tiles * p.nrhs), dim3(64 * kWaves), args, 0, s);
+    if (e != hipSuccess) (void)hipGetLastError();  // (a refusal must not be reported by a later call)
+    return e;
 }
 
 }  // namespace wl

@@ -69,6 +69,15 @@ static bool prefin_enabled() {
     return !(e && std::strcmp(e, "0") == 0);
 }
 
+// The one-launch BiCGStab of small lattices: polls after which a block gives up waiting for the
+// others.  2^21 polls take a second or two, far beyond any wait for blocks that other work on
+// the device holds up and short enough to be lost now and then; 0 turns the one-launch solve off.
+static unsigned one_launch_spins() {
+    const char *e = std::getenv("WILSON_ONE_LAUNCH");
+    if (!e || !*e) return 1u << 21;
+    return (unsigned)std::min(std::strtoul(e, nullptr, 10), 1ul << 24);
+}
+
 size_t EoMem::carve(char *base, const Geom &g, int n, int precision, int method) {
     const int P = inner_prec(precision), PX = P == P16 ? P32 : P;
     const bool mixed = precision != WILSON_FP64;
@@ -123,7 +132,7 @@ class EoCore : public EoMem {
     // bookkeeping of one replay
     bool graphs = false;  // set per call
     bool prefin = false;  // vector kernels may run the finalize before them (set per call)
-    bool small = false;   // BiCGStab solves may run in one launch (set per call)
+    unsigned small = 0;   // BiCGStab solves may run in one launch (set per call): polls of a wait
     // device addresses a captured chunk reads from the gauge field (links of every
     // precision, clover blocks) and its link storage: a cached workspace may be bound to
     // another field, or to a field loaded again at the same host address
@@ -461,7 +470,20 @@ class EoCore : public EoMem {
             // r = rhs - M x  (or rhs), rhat = p = r: the first iteration starts from p as it is
             start_fields(use_x0, x, rhs);
             finalize(FIN_BICG_INIT, 1, nb, sin(), PH_RUN);
-            if (small_fits()) return small_solve(x, maxiter);
+            if (small_fits()) {
+                // Refused, or blocks that did not all run together (a device shared with other
+                // processes, a stream with a CU mask): from the first x again in separate launches.
+                const size_t bytes = (size_t)nk * 12 * spinor_plane_bytes(x.prec, g);
+                if (use_x0) WL_HIP(hipMemcpyAsync(V(x_o.f).data, V(x).data, bytes, hipMemcpyDeviceToDevice, ctx->stream));
+                std::vector<RhsState> fin;
+                if (small_solve(x, maxiter, fin)) return fin;
+                ctx->small_lost = true;
+                if (use_x0) WL_HIP(hipMemcpyAsync(V(x).data, V(x_o.f).data, bytes, hipMemcpyDeviceToDevice, ctx->stream));
+                else WL_HIP(launch_zero(V(x), g, nk, ctx->stream));
+                set_states(sin(), PH_RUN, &active, stop2.data());
+                start_fields(use_x0, x, rhs);
+                finalize(FIN_BICG_INIT, 1, nb, sin(), PH_RUN);
+            }
         } else if (method == WILSON_SOLVER_BLOCK_BICGSTAB_EO) {
             // R = rhs - A X (or rhs), P = R, R~ = R with the column norms, then one phase
             // for the whole block (it runs while any column misses its threshold)
@@ -541,7 +563,7 @@ class EoCore : public EoMem {
     // 1519 / 887; 8^2x16^2 (128 tiles) FP64 1478 / 1180, mixed 1596 / 1116.
     bool small_fits() {
         const int tiles = (g.Vh + 63) / 64;
-        if (!small || !prefin || graphs || ctx->timing || G->has_clover() || (P != P64 && P != P32) || PX != P ||
+        if (!small || ctx->small_lost || !prefin || graphs || ctx->timing || G->has_clover() || (P != P64 && P != P32) || PX != P ||
             tiles > kPreFinMax || blas_nblocks(g, P) > kPreFinMax)
             return false;
         int &cap = ctx->small_blocks[P == P64 ? 0 : 1][G->recon == 12 ? 0 : 1];
@@ -549,7 +571,8 @@ class EoCore : public EoMem {
         return tiles * nk <= cap && hop_config(ctx, hop_args(1, tmp.f, p.f)).dsplit;
     }
 
-    std::vector<RhsState> small_solve(Spinor x, int maxiter) {
+    // false: refused or lost (the fields but b', x_o and the caller's right-hand side are then worthless)
+    bool small_solve(Spinor x, int maxiter, std::vector<RhsState> &st) {
         SmallArgs a;
         std::memset(&a, 0, sizeof a);
         a.g = g;
@@ -562,20 +585,20 @@ class EoCore : public EoMem {
         a.state = S(sin());
         for (int k = 0; k < nk; k++) a.cH[k] = -kap(k) * kap(k);
         a.first = 1;
+        a.spins = small;
         // (the iterations of one launch are bounded, so that no kernel runs for long)
         constexpr int kChunk = 1024;
         for (int done = 0;;) {
             WL_HIP(launch_zero(V(t.f), g, nk, ctx->stream));
             a.iters = std::min(maxiter - done, kChunk);
-            WL_HIP(launch_bicg_small(a, P, G->recon, ctx->stream));
-            std::vector<RhsState> st = read_states(sin());
+            if (launch_bicg_small(a, P, G->recon, ctx->stream) != hipSuccess) return false;
+            st = read_states(sin());
             done += a.iters;
             a.first = 0;
             bool running = false;
             int most = 0;
             for (const RhsState &q : st) {
-                if (q.phase == PH_FAIL && q.fail == FAIL_DEVICE)
-                    throw Error(WILSON_DEVICE_ERROR, "the blocks of a one-launch solve lost each other");
+                if (q.lost) return false;
                 running |= q.phase == PH_RUN;
                 most = std::max(most, q.iter);
             }
@@ -588,7 +611,7 @@ class EoCore : public EoMem {
             ctx->hop_launch_count += 4 * most;
             ctx->bytes_issued += most * (2 * plain + with_y + hop_bytes(h2) + vec_bytes(P, 4 + 3 + 7));
             ctx->flops_issued += 4.0 * most * 1320.0 * g.Vh * nk;
-            return st;
+            return true;
         }
     }
 
@@ -810,7 +833,7 @@ int solve_device(wilson_ctx *ctx, const wilson_gauge *G, double *x_canon, const 
     const Geom &g = C.g;
     C.graphs = prm.graphs && !prm.no_tune && graphs_enabled() && g.Vh <= kGraphMaxVh;
     C.prefin = prefin_enabled();
-    C.small = !prm.reliable;  // (reliable updates resume from p and v)
+    C.small = prm.reliable ? 0 : one_launch_spins();  // (reliable updates resume from p and v)
     C.select(0, nrhs);
     C.kappa.assign(C.nrhs, 0.0);
     std::copy(kappa, kappa + nrhs, C.kappa.begin());

@@ -191,6 +191,16 @@ struct Problem {
         out = device(24 * V * nrhs);
         count.clear();
     }
+    int solve(wilson_solve_info *info, int precision = WILSON_FP64, int use_x0 = 0) {
+        const double kappa = 0.12, tol = 1e-8;
+        wilson_solve_opts o = {};
+        o.precision = precision;
+        o.maxiter = 100;
+        o.use_x0 = use_x0;
+        count.clear();
+        iterated = false;
+        return wilson_solve_ex(ctx, g, out, in, 1, &kappa, &tol, &o, info);
+    }
     int dslash(int parity, int precision, int nrhs = 1) {
         count.clear();
         return wilson_dslash_ex(ctx, g, out, in, 0.12, parity, precision, nrhs);
@@ -220,8 +230,42 @@ static void operator_order() {
     }
 }
 
+// A one-launch solve that is refused, or whose blocks lose each other (also where the state looks
+// finished), goes on in the separate launches, and the context stays with them.
+static void one_launch_lost() {
+    wilson_solve_info info;
+    for (const int how : {0, 1, 2})
+        for (const int precision : {WILSON_FP64, WILSON_FP32}) {
+            Problem p(8, 8, 8, 8);
+            on_small = [&](const SmallArgs &a) {
+                if (how == 1) return hipErrorCooperativeLaunchTooLarge;
+                a.state[0].phase = PH_DONE;
+                a.state[0].iter = 5;
+                a.state[0].lost = how == 2;
+                iterated = how == 0;
+                return hipSuccess;
+            };
+            EXPECT(p.solve(&info, precision) == WILSON_OK && info.converged);
+            EXPECT(count["one_launch"] == 1);
+            EXPECT(info.iterations == (how == 0 ? 5 : 1));
+            EXPECT((count["blas"] > 0) == (how != 0));
+            EXPECT(p.solve(&info, precision, 1) == WILSON_OK);
+            EXPECT(count["one_launch"] == (how == 0 ? 1 : 0));
+        }
+}
+
+// WILSON_ONE_LAUNCH=0
+static void one_launch_off() {
+    wilson_solve_info info;
+    Problem p(8, 8, 8, 8);
+    EXPECT(p.solve(&info) == WILSON_OK && info.converged);
+    EXPECT(count["one_launch"] == 0 && count["blas"] > 0);
+}
+
 int main(int argc, char **argv) {
-    const std::map<std::string, void (*)()> all = {{"operator_order", operator_order}};
+    const std::map<std::string, void (*)()> all = {{"operator_order", operator_order},
+                                                   {"one_launch_lost", one_launch_lost},
+                                                   {"one_launch_off", one_launch_off}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) return 2;
     it->second();

@@ -40,3 +40,8 @@ def run(program, scenario, **env):
 
 def test_operator_keeps_the_order_of_the_tuned_hop(program):
     run(program, "operator_order")
+
+
+def test_lost_one_launch_solve_goes_on_in_separate_launches(program):
+    run(program, "one_launch_lost")
+    run(program, "one_launch_off", WILSON_ONE_LAUNCH="0")
