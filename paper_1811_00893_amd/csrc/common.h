@@ -299,7 +299,8 @@ struct StateInit {
 };
 hipError_t launch_init_states(RhsState *st, const StateInit &init, hipStream_t s);
 
-// BiCGStab iterations on M_ee in one cooperative launch (small lattices, no clover term): one
+// BiCGStab iterations on M_ee in one launch whose blocks wait for each other (small lattices, no
+// clover term; the caller sees to it that the device has room for all of them at once): one
 // block per 64-site tile and right-hand side.  Fields hold nrhs right-hand sides; r, rhat and x
 // are set, p and v count as zero with `first`.  scratch: scratch_stride bytes per right-hand
 // side, the first 256 zero at the launch (barrier counter); state: phases, stop2 and scalars,
@@ -319,7 +320,7 @@ struct SmallArgs {
     double cH[kMaxRhs];  // -kappa^2
 };
 size_t small_scratch_bytes(const Geom &g, int prec);
-// blocks of the kernel the device holds at once (0: not available)
+// CUs of the device, each of which holds a block of the kernel (0: not available)
 int small_max_blocks(int prec, int recon);
 hipError_t launch_bicg_small(const SmallArgs &p, int prec, int recon, hipStream_t s);
 

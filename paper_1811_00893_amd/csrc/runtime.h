@@ -176,7 +176,7 @@ struct wilson_ctx {
     // host resources lent to solves whose device memory the caller provides (created with
     // the context, so those solves allocate nothing themselves)
     wl::SolveHostRes lend;
-    int small_blocks[2][2] = {{-1, -1}, {-1, -1}};  // blocks of the one-launch solve the device holds (FP64 / FP32, 12 / 18 link reals)
+    int small_blocks[2][2] = {{-1, -1}, {-1, -1}};  // small_max_blocks, once asked (FP64 / FP32, 12 / 18 link reals)
     bool small_lost = false;         // a one-launch solve was refused or gave up: this context takes the separate launches
     void *scratch = nullptr;         // device address of the no-allocation solve's array on this device
     hipStream_t capture_stream = nullptr;  // stream that iteration chunks are captured on (HIP graphs)

@@ -14,10 +14,17 @@
 // buffer accesses for fields, relaxed atomics for sums and counters), so they are coherent
 // between the XCDs' L2 caches without writing those back or invalidating them; a block's stores
 // have completed (s_waitcnt) before it arrives at a barrier, and it reads only after it has
-// seen every arrival.  The block's links are the same in every iteration and stay in registers.  The grid is launched cooperatively, so all its blocks are resident; a wait
-// is bounded all the same, and a block that gives up marks the right-hand side as lost: the host
-// then runs the separate launches.  The mark has a word of its own, which no other store touches:
-// tile 0 may still see the last arrivals and store a state that looks finished.
+// seen every arrival.  The block's links are the same in every iteration and stay in registers.
+//
+// The blocks must run together.  It is an ordinary launch: the host keeps the blocks of all such
+// solves in flight on a device within its CUs, and within each XCD's share of them, so there is
+// a place for every block (kernels of other kinds end by themselves and make room).  A
+// cooperative launch gives the same guarantee by running one such grid at a time: four contexts
+// on four streams, 8^4 FP64, 606 us per solve against 194 (368 in separate launches).  Other
+// processes are outside both guarantees, so a wait is bounded all the same, and a block that gives
+// up marks the right-hand side as lost: the host then runs the separate launches.  The mark has a
+// word of its own, which no other store touches: tile 0 may still see the last arrivals and store
+// a state that looks finished.
 //
 // The arithmetic, the order of every sum and the scalar steps are those of the launches it
 // replaces (the direction-split hop, the element-wise vector kernels, the one-wave finalize),
@@ -535,15 +542,14 @@ size_t small_scratch_bytes(const Geom &g, int prec) {
 
 int small_max_blocks(int prec, int recon) {
     const void *k = small_kernel(prec, recon);
-    int dev = 0, cus = 0, coop = 0, per = 0;
+    int dev = 0, cus = 0, per = 0;
     if (!k || hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, 64 * kWaves, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
-    return per * cus;
+    return per > 0 ? cus : 0;  // (one per CU: blocks of several such kernels can then be placed in any mix)
 }
 
 hipError_t launch_bicg_small(const SmallArgs &p, int prec, int recon, hipStream_t s) {
@@ -554,7 +560,7 @@ hipError_t launch_bicg_small(const SmallArgs &p, int prec, int recon, hipStream_
         return hipErrorInvalidValue;
     SmallArgs a = p;
     void *args[] = {&a};
-    const hipError_t e = hipLaunchCooperativeKernel(k, dim3(p.tiles * p.nrhs), dim3(64 * kWaves), args, 0, s);
+    const hipError_t e = hipLaunchKernel(k, dim3(p.tiles * p.nrhs), dim3(64 * kWaves), args, 0, s);
     if (e != hipSuccess) (void)hipGetLastError();  // (a refusal must not be reported by a later call)
     return e;
 }

@@ -3,6 +3,7 @@
 #include "solver.h"
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdlib>
@@ -77,6 +78,31 @@ static unsigned one_launch_spins() {
     if (!e || !*e) return 1u << 21;
     return (unsigned)std::min(std::strtoul(e, nullptr, 10), 1ul << 24);
 }
+
+// Room on each device for the blocks of one-launch solves, which wait for each other: those of all
+// contexts in flight stay within the CUs.  Blocks are dealt to the 8 XCDs in turn, so a solve
+// counts with whole rounds and no XCD is asked for more than its share.  Held until the host has
+// waited for the launch; a solve that finds no room takes the separate launches.
+struct SmallRoom {
+    static constexpr int kDevices = 64;
+    static std::atomic<int> used[kDevices];
+    int device = -1, n = 0;
+    bool take(int dev, int blocks, int cus) {
+        if (dev < 0 || dev >= kDevices) return false;
+        n = (blocks + 7) / 8 * 8;
+        int have = used[dev].load();
+        while (have + n <= cus)
+            if (used[dev].compare_exchange_weak(have, have + n)) {
+                device = dev;
+                return true;
+            }
+        return false;
+    }
+    ~SmallRoom() {
+        if (device >= 0) used[device] -= n;
+    }
+};
+std::atomic<int> SmallRoom::used[SmallRoom::kDevices];
 
 size_t EoMem::carve(char *base, const Geom &g, int n, int precision, int method) {
     const int P = inner_prec(precision), PX = P == P16 ? P32 : P;
@@ -470,7 +496,8 @@ class EoCore : public EoMem {
             // r = rhs - M x  (or rhs), rhat = p = r: the first iteration starts from p as it is
             start_fields(use_x0, x, rhs);
             finalize(FIN_BICG_INIT, 1, nb, sin(), PH_RUN);
-            if (small_fits()) {
+            SmallRoom room;
+            if (small_fits() && room.take(ctx->device, (g.Vh + 63) / 64 * nk, small_cus())) {
                 // Refused, or blocks that did not all run together (a device shared with other
                 // processes, a stream with a CU mask): from the first x again in separate launches.
                 const size_t bytes = (size_t)nk * 12 * spinor_plane_bytes(x.prec, g);
@@ -554,21 +581,24 @@ class EoCore : public EoMem {
         return read_states(sin());
     }
 
-    // Whether this solve's iterations can run in one cooperative launch (small_solve.hip): the
+    // Whether this solve's iterations can run in one launch (small_solve.hip): the
     // lattices whose hops split the directions over waves (the kernel adds them in that order)
-    // and whose partial rows one wave sums, FP64 or FP32, no clover term, every block resident,
+    // and whose partial rows one wave sums, FP64 or FP32, no clover term, no more blocks than CUs,
     // nothing asked for that needs the separate launches (per-launch timing, graphs, separate
     // finalizes).  8^4 FP64: 58 us per iteration in nine launches, 32 in one; whole solves, us,
     // separate launches against one: 8^4 FP64 1 RHS 1230 / 763, 8 RHS 1353 / 895, mixed FP32
     // 1519 / 887; 8^2x16^2 (128 tiles) FP64 1478 / 1180, mixed 1596 / 1116.
+    int small_cus() {
+        int &cus = ctx->small_blocks[P == P64 ? 0 : 1][G->recon == 12 ? 0 : 1];
+        if (cus < 0) cus = small_max_blocks(P, G->recon);
+        return cus;
+    }
     bool small_fits() {
         const int tiles = (g.Vh + 63) / 64;
         if (!small || ctx->small_lost || !prefin || graphs || ctx->timing || G->has_clover() || (P != P64 && P != P32) || PX != P ||
             tiles > kPreFinMax || blas_nblocks(g, P) > kPreFinMax)
             return false;
-        int &cap = ctx->small_blocks[P == P64 ? 0 : 1][G->recon == 12 ? 0 : 1];
-        if (cap < 0) cap = small_max_blocks(P, G->recon);
-        return tiles * nk <= cap && hop_config(ctx, hop_args(1, tmp.f, p.f)).dsplit;
+        return tiles * nk <= small_cus() && hop_config(ctx, hop_args(1, tmp.f, p.f)).dsplit;
     }
 
     // false: refused or lost (the fields but b', x_o and the caller's right-hand side are then worthless)

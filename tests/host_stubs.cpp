@@ -262,10 +262,43 @@ static void one_launch_off() {
     EXPECT(count["one_launch"] == 0 && count["blas"] > 0);
 }
 
+// One-launch solves in flight in several contexts share the device's room: what does not fit takes
+// the separate launches, and the room comes back.
+static void one_launch_room() {
+    favourite = [](const LaunchCfg &c) { return c.dsplit == 1; };
+    Problem a(8, 8, 16, 16), b(8, 8, 16, 16), c(4, 4, 4, 4);  // 128, 128 and 1 blocks of 256
+    std::vector<Problem *> next;
+    int total = 0;
+    on_small = [&](const SmallArgs &s) {
+        total++;
+        if (!next.empty()) {  // (while this one is in flight)
+            Problem *p = next.back();
+            next.pop_back();
+            wilson_solve_info info;
+            EXPECT(p->solve(&info) == WILSON_OK);
+        }
+        s.state[0].phase = PH_DONE;
+        iterated = true;
+        return hipSuccess;
+    };
+    for (int round = 0; round < 2; round++) {
+        wilson_solve_info info;
+        total = 0;
+        next = {&c, &b};
+        EXPECT(a.solve(&info) == WILSON_OK);
+        EXPECT(next.empty() && total == 2);
+        total = 0;
+        next = {&c};
+        EXPECT(b.solve(&info) == WILSON_OK);
+        EXPECT(next.empty() && total == 2);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> all = {{"operator_order", operator_order},
                                                    {"one_launch_lost", one_launch_lost},
-                                                   {"one_launch_off", one_launch_off}};
+                                                   {"one_launch_off", one_launch_off},
+                                                   {"one_launch_room", one_launch_room}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) return 2;
     it->second();

@@ -45,3 +45,7 @@ def test_operator_keeps_the_order_of_the_tuned_hop(program):
 def test_lost_one_launch_solve_goes_on_in_separate_launches(program):
     run(program, "one_launch_lost")
     run(program, "one_launch_off", WILSON_ONE_LAUNCH="0")
+
+
+def test_one_launch_solves_share_the_room_of_the_device(program):
+    run(program, "one_launch_room")
