@@ -97,34 +97,30 @@ wilson_ctx *default_ctx() {
 
 // Packs canonical links into G (dims and geometry set), reusing its buffers where they fit.
 // recon 12 asks for two-row storage, which needs exact SU(3) links (to well below the FP64
-// parity tolerance): the pack checks them on the way, and anything else is packed again in
-// full.  recon 18 keeps every link in full and checks nothing.
+// parity tolerance): anything else is kept in full.  recon 18 keeps every link in full.
 void pack_gauge(wilson_ctx *ctx, wilson_gauge *G, const double *U, uint32_t precisions, int recon) {
     const size_t links = (size_t)72 * G->dims[0] * G->dims[1] * G->dims[2] * G->dims[3];  // doubles
     DevBuf tmp;
     Staged su(ctx, tmp, U, links * sizeof(double), true);
-    auto pack = [&](int rc, int *flag) {
-        void *dst[3];
-        for (int prec = 0; prec < 3; prec++) {
-            const bool want = prec == P64 || (prec == P32 && (precisions & WILSON_GAUGE_FP32)) ||
-                              (prec == P16 && (precisions & WILSON_GAUGE_FP16));
-            const size_t need = gauge_bytes(prec, rc, G->g);
-            if (want && G->U[prec].size() < need) G->U[prec].alloc(need);
-            dst[prec] = want ? G->U[prec].get() : nullptr;
-        }
-        WL_HIP(launch_gauge_pack(dst, su.dev, G->g, rc, 1e-13, flag, ctx->stream));
-        G->recon = rc;
-    };
     if (recon == 12) {
         // (the flag is host-mapped: nothing is copied to clear or to read it)
         if (ctx->pinned.size() < sizeof(int)) ctx->pinned.alloc(256);
         volatile int *bad = static_cast<volatile int *>(ctx->pinned.host());
         *bad = 0;
-        pack(12, static_cast<int *>(ctx->pinned.dev()));
+        WL_HIP(launch_su3_check(su.dev, links / 18, 1e-13, static_cast<int *>(ctx->pinned.dev()), ctx->stream));
         WL_HIP(hipStreamSynchronize(ctx->stream));
         if (*bad) recon = 18;
     }
-    if (recon == 18) pack(18, nullptr);
+    void *dst[3];
+    for (int prec = 0; prec < 3; prec++) {
+        const bool want = prec == P64 || (prec == P32 && (precisions & WILSON_GAUGE_FP32)) ||
+                          (prec == P16 && (precisions & WILSON_GAUGE_FP16));
+        const size_t need = gauge_bytes(prec, recon, G->g);
+        if (want && G->U[prec].size() < need) G->U[prec].alloc(need);
+        dst[prec] = want ? G->U[prec].get() : nullptr;
+    }
+    WL_HIP(launch_gauge_pack(dst, su.dev, G->g, recon, ctx->stream));
+    G->recon = recon;
     WL_HIP(hipStreamSynchronize(ctx->stream));
 }
 

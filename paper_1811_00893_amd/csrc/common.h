@@ -343,11 +343,8 @@ hipError_t launch_axpy_f64(Spinor x64, Spinor e, const Geom &g, int nrhs, const 
 // Gauge: canonical complex128 links -> parity-split planes, in every precision with a
 // destination in dst (indexed by Prec).
 // recon 18: all 9 entries, t-boundary sign folded in; recon 12: rows 0 and 1 only, no sign.
-// flag (optional, device or host-mapped int): set to 1 if a link is off SU(3) by more than tol
-// (max |U U^dag - 1|, |det U - 1|).
-hipError_t launch_gauge_pack(void *const dst[3], const double *canon, const Geom &g, int recon, double tol, int *flag,
-                             hipStream_t s);
-// Sets *flag (device int) to 1 if any canonical link deviates from SU(3) by more than tol
+hipError_t launch_gauge_pack(void *const dst[3], const double *canon, const Geom &g, int recon, hipStream_t s);
+// Sets *flag (device or host-mapped int) to 1 if any canonical link deviates from SU(3) by more than tol
 // (max |U U^dag - 1|, |det U - 1|).
 hipError_t launch_su3_check(const double *canon, size_t nlinks, double tol, int *flag, hipStream_t s);
 // Link planes: 16-byte elements of 1 (FP64) or 2 (FP32) complex, 8-byte elements of 2

@@ -221,10 +221,9 @@ __device__ __forceinline__ double su3_deviation(const Cx<double> (&u)[3][3]) {
     return fmax(dev, fabs(det.re - 1.0) + fabs(det.im));
 }
 
-// Canonical links -> parity-split planes in up to three precisions, with the SU(3) check
-// (CHECK) on the way: one pass over the links (576 B a site, the largest input of the
-// library) where the check and each precision had a pass of its own, and those packed with
-// lanes 1152 B apart on the canonical side.  A block takes 32 checkerboard sites of each
+// Canonical links -> parity-split planes in up to three precisions: one pass over the links
+// (576 B a site, the largest input of the library) where each precision had a pass of its
+// own with lanes 1152 B apart on the canonical side.  A block takes 32 checkerboard sites of each
 // parity = 64 consecutive sites = 36 KB through LDS (rows padded by one element) and writes
 // runs of 32 elements of each plane.  16^3 x 32, FP64, 18 reals a link: 32 us (4.7 TB/s).
 constexpr int kPackSites = 32;
@@ -254,9 +253,8 @@ __device__ __forceinline__ void pack_planes(void *dst, const double2 *buf, const
     }
 }
 
-template <bool CHECK>
 __global__ void __launch_bounds__(256) gauge_pack_kernel(void *d64, void *d32, void *d16, const double2 *canon, Geom g,
-                                                         int recon, double tol, int *flag) {
+                                                         int recon) {
     __shared__ __align__(16) double2 buf[2 * kPackSites * kPackRow];
     __shared__ unsigned char info[kPackSites];  // bit 0: x of the even-parity site is odd; bit 1: t = Lt - 1
     const int tid = threadIdx.x, i0 = blockIdx.x * kPackSites;
@@ -275,29 +273,32 @@ __global__ void __launch_bounds__(256) gauge_pack_kernel(void *d64, void *d32, v
         info[tid] = (unsigned char)(c.b | (c.t == g.L[3] - 1 ? 2 : 0));
     }
     __syncthreads();
-    if constexpr (CHECK) {
-        if ((tid >> 2) < 2 * n) {
-            const double2 *l = buf + (tid >> 2) * kPackRow + (tid & 3) * 9;
-            Cx<double> u[3][3];
-#pragma unroll
-            for (int e = 0; e < 9; e++) u[e / 3][e % 3] = {l[e].x, l[e].y};
-            if (!(su3_deviation(u) <= tol)) *flag = 1;  // (host-mapped; every writer stores the same word)
-        }
-    }
     if (d64) pack_planes<P64>(d64, buf, info, g, i0, n, recon);
     if (d32) pack_planes<P32>(d32, buf, info, g, i0, n, recon);
     if (d16) pack_planes<P16>(d16, buf, info, g, i0, n, recon);
 }
 
-// flags any link off SU(3) by more than tol
-__global__ void su3_check_kernel(const double2 *canon, size_t nlinks, double tol, int *flag) {
-    bool bad = false;
-    for (size_t l = blockIdx.x * (size_t)blockDim.x + threadIdx.x; l < nlinks; l += (size_t)gridDim.x * blockDim.x) {
-        Cx<double> u[3][3];
-        for (int e = 0; e < 9; e++) u[e / 3][e % 3] = {canon[l * 9 + e].x, canon[l * 9 + e].y};
-        bad |= !(su3_deviation(u) <= tol);
+// Sets *flag if any link is off SU(3) by more than tol.  256 links a block, read in whole runs
+// through LDS.  A pass of its own before the packing, not part of it, so that how links are stored
+// is known before buffers are made: a load in three precisions, 16^4, links in full, 390 us, and 1340
+// when buffers for two rows were made first (two rows at 24^3 x 48: 870, 750 with the check inside
+// the packing).
+__global__ void __launch_bounds__(256) su3_check_kernel(const double2 *canon, size_t nlinks, double tol, int *flag) {
+    __shared__ __align__(16) double2 buf[256 * 9];
+    const size_t l0 = (size_t)blockIdx.x * 256;
+    const int n = (int)(nlinks - l0 < 256 ? nlinks - l0 : 256), tid = threadIdx.x;
+    const double2 *src = canon + l0 * 9;
+#pragma unroll
+    for (int k = 0; k < 9; k++) {
+        const int e = k * 256 + tid;
+        if (e < 9 * n) buf[e] = src[e];
     }
-    if (bad) atomicOr(flag, 1);
+    __syncthreads();
+    if (tid >= n) return;
+    Cx<double> u[3][3];
+#pragma unroll
+    for (int e = 0; e < 9; e++) u[e / 3][e % 3] = {buf[tid * 9 + e].x, buf[tid * 9 + e].y};
+    if (!(su3_deviation(u) <= tol)) *flag = 1;  // (every writer stores the same word)
 }
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -427,19 +428,17 @@ hipError_t launch_axpy_f64(Spinor x64, Spinor e, const Geom &g, int nrhs, const 
     return hipGetLastError();
 }
 
-hipError_t launch_gauge_pack(void *const dst[3], const double *canon, const Geom &g, int recon, double tol, int *flag,
-                             hipStream_t s) {
+hipError_t launch_gauge_pack(void *const dst[3], const double *canon, const Geom &g, int recon, hipStream_t s) {
     if ((recon != 12 && recon != 18) || (!dst[P64] && !dst[P32] && !dst[P16])) return hipErrorInvalidValue;
     const dim3 grid((g.Vh + kPackSites - 1) / kPackSites), block(256);
-    const double2 *c = reinterpret_cast<const double2 *>(canon);
-    if (flag) hipLaunchKernelGGL(gauge_pack_kernel<true>, grid, block, 0, s, dst[P64], dst[P32], dst[P16], c, g, recon, tol, flag);
-    else hipLaunchKernelGGL(gauge_pack_kernel<false>, grid, block, 0, s, dst[P64], dst[P32], dst[P16], c, g, recon, tol, flag);
+    hipLaunchKernelGGL(gauge_pack_kernel, grid, block, 0, s, dst[P64], dst[P32], dst[P16],
+                       reinterpret_cast<const double2 *>(canon), g, recon);
     return hipGetLastError();
 }
 
 hipError_t launch_su3_check(const double *canon, size_t nlinks, double tol, int *flag, hipStream_t s) {
-    hipLaunchKernelGGL(su3_check_kernel, dim3(2048), dim3(256), 0, s, reinterpret_cast<const double2 *>(canon),
-                       nlinks, tol, flag);
+    hipLaunchKernelGGL(su3_check_kernel, dim3((unsigned)((nlinks + 255) / 256)), dim3(256), 0, s,
+                       reinterpret_cast<const double2 *>(canon), nlinks, tol, flag);
     return hipGetLastError();
 }
 

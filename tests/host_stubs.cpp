@@ -27,6 +27,7 @@ static std::function<hipError_t(const SmallArgs &)> on_small;
 static std::function<bool(const LaunchCfg &)> favourite;  // the shape that times best
 static LaunchCfg last_cfg;
 static bool iterated = false;                   // an iteration or a one-launch solve has run
+static bool su3 = true;                         // what the check of links finds
 static double residual = 0.0;                   // norms stored once that is so
 static size_t allocated = 0, limit = ~size_t(0);
 static std::map<void *, size_t> blocks;
@@ -35,6 +36,7 @@ static std::map<void *, size_t> blocks;
 extern "C" {
 hipError_t hipMalloc(void **p, size_t n) {
     if (allocated + n > limit) return hipErrorOutOfMemory;
+    count["malloc"]++;
     *p = std::calloc(1, n);
     blocks[*p] = n;
     allocated += n;
@@ -110,8 +112,11 @@ int split_nblocks(const Geom &g) { return (g.Vh + 127) / 128; }
 hipError_t launch_convert(Spinor, Spinor, const Geom &, int, const RhsState *, int, hipStream_t) { return RECORD("convert"); }
 hipError_t launch_axpy_f64(Spinor, Spinor, const Geom &, int, const RhsState *, int, hipStream_t) { return RECORD("axpy"); }
 hipError_t launch_zero(const Spinor &, const Geom &, int, hipStream_t) { return RECORD("zero"); }
-hipError_t launch_gauge_pack(void *const[3], const double *, const Geom &, int, double, int *, hipStream_t) { return RECORD("pack"); }
-hipError_t launch_su3_check(const double *, size_t, double, int *, hipStream_t) { return RECORD("check"); }
+hipError_t launch_gauge_pack(void *const[3], const double *, const Geom &, int, hipStream_t) { return RECORD("pack"); }
+hipError_t launch_su3_check(const double *, size_t, double, int *flag, hipStream_t) {
+    if (!su3) *flag = 1;
+    return RECORD("check");
+}
 hipError_t launch_clover_pack(void *, void *, void *, void *, const double *, const Geom &, double, int *, hipStream_t) { return RECORD("clover_pack"); }
 hipError_t launch_clover_apply(Spinor, Spinor, const void *, const Geom &, int, hipStream_t) { return RECORD("clover"); }
 hipError_t launch_block_gram(BlockArgs, int, hipStream_t) { return RECORD("gram"); }
@@ -294,11 +299,28 @@ static void one_launch_room() {
     }
 }
 
+// A load makes each buffer once, of the size that its links need, whether they are SU(3) or not.
+static void load_allocates_once() {
+    for (const bool exact : {true, false}) {
+        su3 = exact;
+        Problem p(8, 8, 8, 16);
+        double *U = device(72 * p.V);
+        wilson_gauge *g = nullptr;
+        count.clear();
+        const size_t before = allocated;
+        EXPECT(wilson_gauge_load(p.ctx, &g, U, p.dims, WILSON_GAUGE_FP32 | WILSON_GAUGE_FP16) == WILSON_OK);
+        EXPECT(count["malloc"] == 3 && count["pack"] == 1 && count["check"] == 1);
+        EXPECT(allocated - before == wilson_gauge_bytes(g));
+        EXPECT(wilson_gauge_bytes(g) == wilson_gauge_footprint_bytes(p.dims, 7, exact ? 12 : 18));
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> all = {{"operator_order", operator_order},
                                                    {"one_launch_lost", one_launch_lost},
                                                    {"one_launch_off", one_launch_off},
-                                                   {"one_launch_room", one_launch_room}};
+                                                   {"one_launch_room", one_launch_room},
+                                                   {"load_allocates_once", load_allocates_once}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) return 2;
     it->second();

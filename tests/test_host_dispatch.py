@@ -49,3 +49,7 @@ def test_lost_one_launch_solve_goes_on_in_separate_launches(program):
 
 def test_one_launch_solves_share_the_room_of_the_device(program):
     run(program, "one_launch_room")
+
+
+def test_a_load_makes_each_buffer_once(program):
+    run(program, "load_allocates_once")
