@@ -479,12 +479,12 @@ LaunchCfg hop_config(wilson_ctx *ctx, const HopArgs &a) {
     return fit_cfg(a, cfg);
 }
 
-int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes) {
+int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes, const LaunchCfg *shape) {
     if (a.nrhs < 1 || a.nrhs > kMaxRhs) throw Error(WILSON_INVALID_ARG, "nrhs out of range");
     if (a.out.data == a.in.data || (a.has_y && a.out.data == a.y.data) || (a.has_z && a.out.data == a.z.data))
         throw Error(WILSON_INVALID_ARG, "hop output aliases an input");
     if (a.clov_mode != CLV_NONE && a.clov == nullptr) throw Error(WILSON_INVALID_ARG, "clover blocks missing");
-    const LaunchCfg cfg = hop_config(ctx, a);
+    const LaunchCfg cfg = shape ? *shape : hop_config(ctx, a);
     ctx->hop_launch_count++;
     ctx->bytes_issued += algorithmic_bytes;
     ctx->flops_issued += (a.clov_mode != CLV_NONE ? 1896.0 : 1320.0) * a.g.Vh * a.nrhs;

@@ -200,9 +200,11 @@ namespace wl {
 
 // Launch a parity hop with the tuned configuration, timed if timing is on.
 // algorithmic_bytes is the per-launch byte count used for achieved-bandwidth figures.
-// Returns the number of blocks launched (the row length of the partials it wrote).
-int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes);
-// The launch shape a hop takes (pinned, tuned now or earlier, or the default).
+// Returns the number of blocks launched (the row length of the partials it wrote).  shape: as
+// hop_config gave it (null: looked up here).
+int hop(wilson_ctx *ctx, HopArgs &a, double algorithmic_bytes, const LaunchCfg *shape = nullptr);
+// The launch shape a hop takes (pinned, tuned now or earlier, or the default).  Where no tuning
+// may run, the next call can give another one: a context of another thread may tune meanwhile.
 LaunchCfg hop_config(wilson_ctx *ctx, const HopArgs &a);
 // Whether a launch shape is pinned for this context (WILSON_HOP_CFG).
 bool hop_pinned(wilson_ctx *ctx);

@@ -441,24 +441,28 @@ class EoCore : public EoMem {
         run_hop(a);
     }
     // |b - D x|^2 of the full system into sout()[].aux (nothing stored); the two parities'
-    // partials share one row
+    // partials share one row, so both hops take the launch shape looked up for the first
     void true_residual2() {
+        LaunchCfg shape;
         int nb = 0;
         for (int par = 0; par < 2; par++) {
-            HopArgs a = hop_args(par, par ? tmp64_or_scratch() : tmp64_or_scratch(), par ? x_e.f : x_o.f);
+            HopArgs a = hop_args(par, tmp64_or_scratch(), par ? x_e.f : x_o.f);
             a.nostore = 1;
+            for (int k = 0; k < nk; k++) a.cH[k] = kap(k);
             a.has_y = 1; a.y = V(par ? b_o.f : b_e.f);
             a.has_z = 1; a.z = V(par ? x_o.f : x_e.f); a.cz = -1.0;
-            for (int k = 0; k < nk; k++) a.cH[k] = kap(k);
             if (G->has_clover()) {  // b - T x + k H x
                 a.clov = G->clover(false, P64, par);
                 a.clov_mode = CLV_Z;
             }
             a.red = RED_NORM2;
-            if (par == 0) nb = hop_nblocks(a, hop_config(ctx, a));
+            if (par == 0) {
+                shape = hop_config(ctx, a);
+                nb = hop_nblocks(a, shape);
+            }
             a.pstride = 2 * nb;
             a.partials = part() + par * nb;
-            if (run_hop(a) != nb) throw Error(WILSON_DEVICE_ERROR, "the hops of one residual differ in shape");
+            hop(ctx, a, hop_bytes(a), &shape);
         }
         finalize(FIN_STORE_AUX, 1, 2 * nb, sout(), kAllPhases);
     }

@@ -74,7 +74,11 @@ hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorName(hipError_t) { return "error"; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
-hipError_t hipGetSymbolAddress(void **p, const void *) { static char one; *p = &one; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) {
+    static void *scratch = std::calloc(1, size_t(256) << 20);
+    *p = scratch;
+    return hipSuccess;
+}
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p) {
     for (const auto &b : blocks)
         if (p >= b.first && p < static_cast<char *>(b.first) + b.second) {
@@ -315,12 +319,38 @@ static void load_allocates_once() {
     }
 }
 
+// Another thread's context tunes the shape of a running solve that may not tune itself, between any
+// two of its hops: the solve succeeds.
+static void shape_changes() {
+    favourite = [](const LaunchCfg &c) { return c.block == 64; };
+    wilson_solve_info info;
+    Problem p(8, 8, 16, 32);
+    TuneTable &T = tune_table();
+    EXPECT(p.solve(&info) == WILSON_OK && T.cfg.size() == 1);
+    const auto tuned = *T.cfg.begin();
+    EXPECT(tuned.second.block == 64);
+    const double kappa = 0.12, tol = 1e-8;
+    for (int at = 0, hops = 1; at < hops; at++) {
+        T.cfg.clear();
+        Problem q(8, 8, 16, 32);
+        iterated = false;
+        hops = 0;
+        on_hop = [&](const HopArgs &, const LaunchCfg &) {
+            if (hops++ == at) T.cfg.insert(tuned);
+        };
+        EXPECT(wilson_solve_noalloc(q.ctx, q.g, q.out, q.in, 1, &kappa, &tol, nullptr, &info) == WILSON_OK);
+        EXPECT(hops > 6 && info.converged);
+        on_hop = nullptr;
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> all = {{"operator_order", operator_order},
                                                    {"one_launch_lost", one_launch_lost},
                                                    {"one_launch_off", one_launch_off},
                                                    {"one_launch_room", one_launch_room},
-                                                   {"load_allocates_once", load_allocates_once}};
+                                                   {"load_allocates_once", load_allocates_once},
+                                                   {"shape_changes", shape_changes}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) return 2;
     it->second();

@@ -53,3 +53,7 @@ def test_one_launch_solves_share_the_room_of_the_device(program):
 
 def test_a_load_makes_each_buffer_once(program):
     run(program, "load_allocates_once")
+
+
+def test_a_shape_tuned_during_a_solve_does_not_fail_it(program):
+    run(program, "shape_changes")
