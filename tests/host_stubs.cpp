@@ -75,7 +75,7 @@ hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorName(hipError_t) { return "error"; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
 hipError_t hipGetSymbolAddress(void **p, const void *) {
-    static void *scratch = std::calloc(1, size_t(256) << 20);
+    static void *scratch = std::aligned_alloc(256, size_t(256) << 20);  // (touched only where the host reads)
     *p = scratch;
     return hipSuccess;
 }
@@ -338,7 +338,9 @@ static void shape_changes() {
         on_hop = [&](const HopArgs &, const LaunchCfg &) {
             if (hops++ == at) T.cfg.insert(tuned);
         };
-        EXPECT(wilson_solve_noalloc(q.ctx, q.g, q.out, q.in, 1, &kappa, &tol, nullptr, &info) == WILSON_OK);
+        const int st = wilson_solve_noalloc(q.ctx, q.g, q.out, q.in, 1, &kappa, &tol, nullptr, &info);
+        if (st != WILSON_OK) std::printf("tuned at hop %d: %s\n", at, wilson_last_error());
+        EXPECT(st == WILSON_OK);
         EXPECT(hops > 6 && info.converged);
         on_hop = nullptr;
     }
