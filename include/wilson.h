@@ -338,7 +338,12 @@ int wilson_batch_detach(wilson_batch *batch, int32_t slot, double *x, wilson_sol
 typedef enum { WILSON_KERNEL_HOP = 0, WILSON_KERNEL_BLAS = 1, WILSON_KERNEL_COUNT = 2 } wilson_kernel_class;
 
 /* Enable (1) / disable (0) event timing of every launch of the timed kernel classes
- * on the context's stream; enabling clears the accumulators. */
+ * on the context's stream; enabling clears the accumulators.  While it is on, every call
+ * runs the launches that the classes name: wilson_dslash_ex the solvers' parity hop between
+ * layout conversions, and a solve on a small lattice its separate launches, where either may
+ * otherwise take a kernel that does several of those steps at once.  The FP32 and FP16 results
+ * are the same to the bit; FP64 Dslash results may differ in the last bits, as they may
+ * between launch shapes (the order in which the directions are added). */
 int wilson_timing_enable(wilson_ctx *ctx, int32_t enable);
 /* Sum of launch durations (ms), launch count and algorithmic bytes of a kernel class
  * since timing was enabled.  Waits for outstanding timed work. */

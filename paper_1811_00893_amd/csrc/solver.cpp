@@ -1205,9 +1205,10 @@ void dslash_device(wilson_ctx *ctx, const wilson_gauge *G, double *out, const do
     a.in.prec = P;
     a.has_y = parity == 2;
     for (int k = 0; k < nrhs; k++) a.cH[k] = -kappa;
-    // The operator kernels run without a clover term (its epilogue stays with the hops) and
-    // not where a launch shape is pinned (the pinned hop is what such a context asks for).
-    const bool own = !hop_pinned(ctx) && !(parity == 2 && G->has_clover());
+    // The operator kernels run without a clover term (its epilogue stays with the hops), not
+    // where a launch shape is pinned (the pinned hop is what such a context asks for) and not
+    // under per-launch timing (what the hop class times is the solvers' hop).
+    const bool own = !ctx->timing && !hop_pinned(ctx) && !(parity == 2 && G->has_clover());
     FullArgs f;
     std::memset(&f, 0, sizeof f);
     f.g = g;
@@ -1219,11 +1220,6 @@ void dslash_device(wilson_ctx *ctx, const wilson_gauge *G, double *out, const do
     f.gprec = a.gprec;
     f.recon = a.recon;
     f.cH = -kappa;
-    auto run_own = [&](int parities, auto &&launch) {
-        ctx->hop_launch_count++;
-        ctx->flops_issued += 1320.0 * g.Vh * nrhs * parities;
-        timed_launch(ctx, WILSON_KERNEL_HOP, parities * hop_bytes(a), launch);
-    };
     // planes for every form of the call, made at a shape's first call (a later one may be captured)
     const wilson_ctx::DslashKey key = {{G->dims[0], G->dims[1], G->dims[2], G->dims[3]}, P, nrhs};
     if (!ctx->dslash_ws || !(ctx->dslash_key == key)) {
@@ -1241,7 +1237,7 @@ void dslash_device(wilson_ctx *ctx, const wilson_gauge *G, double *out, const do
     const bool apart = out == in || out + n <= in || in + n <= out;
     const bool small = (size_t)g.Vh * np * nrhs <= kSmallSites && (P == P64 || g.Vh < kSmallVhLow);
     if (own && small && apart) {
-        run_own(np, [&]() { return launch_dslash_small(f, P, ctx->stream); });
+        WL_HIP(launch_dslash_small(f, P, ctx->stream));
         return;
     }
     if (parity == 2) WL_HIP(launch_split(ws->in[0].f, ws->in[1].f, in, g, nrhs, ctx->stream));
@@ -1249,13 +1245,12 @@ void dslash_device(wilson_ctx *ctx, const wilson_gauge *G, double *out, const do
     // D on one right-hand side in one launch, and hops of several that write the canonical layout
     // themselves (one parity of 12 FP32 RHS at 24^3x48: 628 us against 727 through the hop's
     // planes).  FP32 and FP16 fields keep to the hop where its tuned shape adds the directions in
-    // another order (as for the small kernel).  Under per-launch timing the solvers' hop of
-    // several right-hand sides runs between the conversions, as it is what the hop class times.
+    // another order (as for the small kernel).
     a.par = parity == 2 ? 0 : parity;
     a.out = ws->out[a.par].f;
     a.in = ws->in[1 - a.par].f;
     if (parity == 2) a.y = ws->in[0].f;
-    bool canon = own && (nrhs == 1 ? parity == 2 : !ctx->timing);
+    bool canon = own && (nrhs > 1 || parity == 2);
     if (canon && P != P64) {
         const LaunchCfg c = hop_config(ctx, a);
         canon = !c.dsplit && !c.tm;
@@ -1264,12 +1259,11 @@ void dslash_device(wilson_ctx *ctx, const wilson_gauge *G, double *out, const do
         f.f[0] = ws->in[0].f;
         f.f[1] = ws->in[1].f;
         if (nrhs == 1) {
-            run_own(2, [&]() { return launch_dslash_full(f, ctx->stream); });
+            WL_HIP(launch_dslash_full(f, ctx->stream));
             return;
         }
         for (int par = 0; par < 2; par++)
-            if (parity == 2 || parity == par)
-                run_own(1, [&]() { return launch_dslash_rhs(f, par, parity == 2, ctx->stream); });
+            if (parity == 2 || parity == par) WL_HIP(launch_dslash_rhs(f, par, parity == 2, ctx->stream));
         return;
     }
     for (int par = 0; par < 2; par++) {

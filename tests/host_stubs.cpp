@@ -346,13 +346,40 @@ static void shape_changes() {
     }
 }
 
+// What the hop class times is the solvers' hop, in every form of the operator call and in solves
+// that would otherwise take one launch.
+static void timed_calls() {
+    for (const int z : {8, 32}) {
+        Problem p(8, 8, 8, z, 5);
+        for (const bool timed : {false, true}) {
+            EXPECT(wilson_timing_enable(p.ctx, timed) == WILSON_OK);
+            for (int parity = 0; parity < 3; parity++)
+                for (const int precision : {WILSON_FP64, WILSON_FP32, WILSON_FP16, WILSON_FP16_L32})
+                    for (const int nrhs : {1, 2, 5}) {
+                        EXPECT(p.dslash(parity, precision, nrhs) == WILSON_OK);  // (may tune)
+                        double ms, bytes;
+                        int64_t n0, n1;
+                        EXPECT(wilson_timing_read(p.ctx, WILSON_KERNEL_HOP, &ms, &n0, &bytes) == WILSON_OK);
+                        EXPECT(p.dslash(parity, precision, nrhs) == WILSON_OK);
+                        EXPECT(wilson_timing_read(p.ctx, WILSON_KERNEL_HOP, &ms, &n1, &bytes) == WILSON_OK);
+                        if (!timed) continue;
+                        EXPECT(count["hop"] == (parity == 2 ? 2 : 1) && n1 - n0 == count["hop"]);
+                        EXPECT(count["small"] + count["full"] + count["rhs"] == 0);
+                    }
+        }
+        wilson_solve_info info;
+        EXPECT(p.solve(&info) == WILSON_OK && count["one_launch"] == 0);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> all = {{"operator_order", operator_order},
                                                    {"one_launch_lost", one_launch_lost},
                                                    {"one_launch_off", one_launch_off},
                                                    {"one_launch_room", one_launch_room},
                                                    {"load_allocates_once", load_allocates_once},
-                                                   {"shape_changes", shape_changes}};
+                                                   {"shape_changes", shape_changes},
+                                                   {"timed_calls", timed_calls}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) return 2;
     it->second();

@@ -57,3 +57,7 @@ def test_a_load_makes_each_buffer_once(program):
 
 def test_a_shape_tuned_during_a_solve_does_not_fail_it(program):
     run(program, "shape_changes")
+
+
+def test_timed_calls_run_the_hop(program):
+    run(program, "timed_calls")
