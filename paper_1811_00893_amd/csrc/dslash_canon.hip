@@ -44,6 +44,18 @@ __device__ __forceinline__ void as_stored(Cx<R> (&o)[12]) {
     }
 }
 
+// o + y as the hop's epilogue forms it: there o is rounded before a branch that adds y; here the
+// compiler would fuse the product that made o into the sum, and FP32 and FP16 results would
+// change in their last bits with the kernel (FP64 keeps the fused form).
+template <int SP, typename R>
+__device__ __forceinline__ void add_term(Cx<R> (&o)[12], const Cx<R> (&y)[12]) {
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        if constexpr (SP != P64) asm volatile("" : "+v"(o[k].re), "+v"(o[k].im));
+        o[k] = cadd(o[k], y[k]);
+    }
+}
+
 constexpr int kCanonRow = 13;  // padded LDS row of one site: 12 complex and one unused
 
 // A block holds 128 checkerboard sites of each parity (waves 0, 1 even, 2, 3 odd): the 256
@@ -83,7 +95,8 @@ dslash_full_kernel(const FullArgs p, const VisitOrder vo) {
 #pragma unroll
     for (int s = 0; s < 4; s++)
 #pragma unroll
-        for (int k = 0; k < 3; k++) o[s * 3 + k] = cadd(cscale(acc[0][s][k], cH), y[s * 3 + k]);
+        for (int k = 0; k < 3; k++) o[s * 3 + k] = cscale(acc[0][s][k], cH);
+    add_term<SP>(o, y);
     as_stored<SP, R>(o);
     if (l < n) {
 #pragma unroll
@@ -147,8 +160,7 @@ dslash_rhs_kernel(const FullArgs p, int par, int has_y, const VisitOrder vo) {
     if (has_y) {
         Cx<R> y[12];
         load_site<SP, R, true>(y, fp, g.stride, rhs, i);
-#pragma unroll
-        for (int k = 0; k < 12; k++) o[k] = cadd(o[k], y[k]);
+        add_term<SP>(o, y);
     }
     as_stored<SP, R>(o);
     if constexpr (LL) __syncthreads();  // every wave has read the links
@@ -278,8 +290,8 @@ __global__ void __launch_bounds__(320) dslash_small_kernel(const FullArgs p) {
                          ((part[0][2 * k + 1][lane] + part[1][2 * k + 1][lane]) + part[2][2 * k + 1][lane]) +
                              part[3][2 * k + 1][lane]};
         o[k] = cscale(t, cH);
-        if (p.par == 2) o[k] = cadd(o[k], y[k]);
     }
+    if (p.par == 2) add_term<SP>(o, y);
     as_stored<SP, R>(o);
     if (!valid) return;
     dvec2 *dst = reinterpret_cast<dvec2 *>(p.out) + ((size_t)rhs * g.Vh * 2 + 2 * (size_t)i + c.b) * 12;
