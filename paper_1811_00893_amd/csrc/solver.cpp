@@ -637,7 +637,7 @@ class EoCore : public EoMem {
                 most = std::max(most, q.iter);
             }
             if (running && done < maxiter) continue;
-            // the launches it stands for
+            // its hops and vector steps, counted as their launches would be
             HopArgs h1 = hop_args(1, tmp.f, p.f), h2 = hop_args(0, v.f, tmp.f);
             h2.has_y = 1;
             const double plain = hop_bytes(h1), with_y = hop_bytes(h2);
