@@ -182,8 +182,9 @@ typedef struct {
  *   parity 2:      out = D * in = in - kappa * H * in on every site; out == in is rejected.
  * out, in: 12*V complex each.  U: 36*V complex (periodic links).  kappa finite.
  * Uses an internal context on the default stream; synchronous.  Its link buffer (up to 512 MiB,
- * one lattice shape and device at a time; the contents are packed from U on every call) stays
- * allocated for the next plain call and is given back when an allocation fails.
+ * one lattice shape and device at a time; the contents are packed from U on every call) and the
+ * half-lattice fields it works on (two thirds as much, so up to 854 MiB with the links) stay
+ * allocated for the next plain call; they are given back when an allocation of the library fails.
  */
 int wilson_dslash(double *out, const double *in, const double *U, double kappa, const int32_t dims[4],
                   int32_t parity);

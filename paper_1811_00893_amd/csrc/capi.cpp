@@ -89,12 +89,6 @@ wilson_ctx *make_ctx(void *stream) {
     return c.release();
 }
 
-wilson_ctx *default_ctx() {
-    std::lock_guard<std::mutex> lk(g_default_mu);
-    if (!g_default_ctx) g_default_ctx = make_ctx(nullptr);
-    return g_default_ctx;
-}
-
 // Packs canonical links into G (dims and geometry set), reusing its buffers where they fit.
 // recon 12 asks for two-row storage, which needs exact SU(3) links (to well below the FP64
 // parity tolerance): anything else is kept in full.  recon 18 keeps every link in full.
@@ -146,59 +140,74 @@ wilson_gauge *load_gauge(wilson_ctx *ctx, const double *U, const int32_t *dims, 
 }
 
 // The plain entry points take the links with every call.  Their packed links live in one
-// field kept with the default context (guarded by g_default_mu, like that context), so that a
-// program calling them in a loop does not allocate and free device memory each time: the
-// links are packed anew by every call, only the buffers stay.  Another shape or device
-// replaces them, a field of more than kPlainKeep bytes is released when its call ends, and
-// they are given back when an allocation of the library fails.
+// field kept with the default context, so that a program calling them in a loop does not
+// allocate and free device memory each time: the links are packed anew by every call, only the
+// buffers stay, and with them the Dslash planes of the shape (384 B a site beside 576).
+// Another shape or device replaces them, a field of more than kPlainKeep bytes is released with
+// its planes when its call ends, and both are given back when an allocation of the library fails.
 constexpr size_t kPlainKeep = size_t(512) << 20;
 wilson_gauge *g_plain = nullptr;
 int g_plain_device = 0;
-thread_local bool tl_in_plain = false;
 
-// the field and the Dslash planes of its shape (g_default_mu held)
+// What a failing allocation of this thread may take: outside a plain call the field and the
+// planes; inside one only the planes, and only while that call does not use them.
+enum PlainPhase { PLAIN_OUTSIDE, PLAIN_PLANES_FREE, PLAIN_PLANES_USED };
+thread_local PlainPhase tl_plain = PLAIN_OUTSIDE;
+
+bool drop_planes() {
+    if (!g_default_ctx || !g_default_ctx->dslash_ws) return false;
+    g_default_ctx->dslash_ws.reset();
+    return true;
+}
+// the field and the planes (g_default_mu held)
 void drop_plain() {
-    if (g_default_ctx) g_default_ctx->dslash_ws.reset();
+    drop_planes();
     delete g_plain;
     g_plain = nullptr;
 }
 
 bool reclaim_plain() {
-    if (tl_in_plain) return false;
+    if (tl_plain == PLAIN_PLANES_USED) return false;
+    if (tl_plain == PLAIN_PLANES_FREE) return drop_planes();  // (this thread holds the lock)
     std::unique_lock<std::mutex> lk(g_default_mu, std::try_to_lock);
     if (!lk.owns_lock() || !g_plain) return false;
     drop_plain();
     return true;
 }
 
-struct PlainGauge {
+// A plain call: the lock, the default context and the packed links.
+struct PlainCall {
+    std::lock_guard<std::mutex> lk;
+    struct Phase {
+        Phase() { tl_plain = PLAIN_PLANES_FREE; }
+        ~Phase() { tl_plain = PLAIN_OUTSIDE; }
+    } phase;  // (all of the time that the lock is held: a reclaim by this thread must not ask for it)
+    wilson_ctx *ctx;
     wilson_gauge *G = nullptr;
-    PlainGauge(wilson_ctx *ctx, const double *U, const int32_t *dims, int recon) {
+    PlainCall(const double *U, const int32_t *dims, int recon) : lk(g_default_mu) {
         int dev = 0;
         WL_HIP(hipGetDevice(&dev));
-        tl_in_plain = true;
+        set_reclaim(reclaim_plain);
+        if (!g_default_ctx) g_default_ctx = make_ctx(nullptr);
+        ctx = g_default_ctx;
+        if (g_plain && (g_plain_device != dev || std::memcmp(g_plain->dims, dims, sizeof g_plain->dims) != 0)) drop_plain();
         try {
-            if (g_plain && (g_plain_device != dev || std::memcmp(g_plain->dims, dims, sizeof g_plain->dims) != 0))
-                drop_plain();
             if (!g_plain) {
                 std::unique_ptr<wilson_gauge> made(new wilson_gauge());
                 made->g = make_geom(dims);
                 std::memcpy(made->dims, dims, sizeof made->dims);
                 g_plain = made.release();
                 g_plain_device = dev;
-                set_reclaim(reclaim_plain);
             }
             pack_gauge(ctx, g_plain, U, 0, recon);
         } catch (...) {
-            end(true);
+            drop_plain();
             throw;
         }
         G = g_plain;
     }
-    ~PlainGauge() { end(G->bytes() > kPlainKeep || std::uncaught_exceptions() > 0); }
-    static void end(bool drop) {
-        if (drop) drop_plain();
-        tl_in_plain = false;
+    ~PlainCall() {
+        if (G->bytes() > kPlainKeep || std::uncaught_exceptions() > 0) drop_plain();
     }
 };
 
@@ -416,13 +425,13 @@ int wilson_dslash(double *out, const double *in, const double *U, double kappa, 
     WL_CHECK_ARG(parity >= 0 && parity <= 2, "parity must be 0, 1 or 2");
     WL_CHECK_ARG(!(parity == 2 && out == in), "out == in is not allowed for parity 2");
     WL_CHECK_ARG(std::isfinite(kappa), "kappa must be finite");
-    wilson_ctx *ctx = default_ctx();
-    std::lock_guard<std::mutex> lk(g_default_mu);
     // one application: packing two rows would save less than the SU(3) check costs
-    PlainGauge plain(ctx, U, dims, 18);
+    PlainCall plain(U, dims, 18);
+    wilson_ctx *ctx = plain.ctx;
     const size_t bytes = spinor_doubles(dims, 1) * sizeof(double);
     Staged si(ctx, ctx->stage_in, in, bytes, true);
     Staged so(ctx, ctx->stage_out, out, bytes, parity != 2);
+    tl_plain = PLAIN_PLANES_USED;
     dslash_device(ctx, plain.G, so.dev, si.dev, kappa, parity, WILSON_FP64, 1);
     so.copy_out();
     WL_HIP(hipStreamSynchronize(ctx->stream));
@@ -500,9 +509,8 @@ int wilson_solve(double *x, const double *b, const double *U, double kappa, cons
     WL_CHECK_ARG(maxiter > 0, "maxiter must be > 0");
     WL_CHECK_ARG(x != b, "x and b must be distinct");
     check_solve_args(&kappa, &tol, 1, nullptr);
-    wilson_ctx *ctx = default_ctx();
-    std::lock_guard<std::mutex> lk(g_default_mu);
-    PlainGauge plain(ctx, U, dims, wanted_recon());
+    PlainCall plain(U, dims, wanted_recon());
+    wilson_ctx *ctx = plain.ctx;
     SolveParams p;
     p.maxiter = maxiter;
     const size_t bytes = spinor_doubles(dims, 1) * sizeof(double);

@@ -372,6 +372,34 @@ static void timed_calls() {
     }
 }
 
+// What the plain calls keep on the device: links and planes of one shape, nothing of a large one; and
+// a later plain call gets the planes' memory if it does not fit otherwise, any other call both.
+static void plain_memory() {
+    const int32_t small[4] = {16, 16, 16, 16}, large[4] = {32, 32, 32, 64};
+    const size_t V = 16 * 16 * 16 * 16, VL = 32 * 32 * 32 * 64, links = 576 * V, planes = 384 * V;
+    double *U = device(72 * VL), *in = device(24 * VL), *out = device(24 * VL);
+    const size_t base = allocated;
+    EXPECT(wilson_dslash(out, in, U, 0.1, large, 2) == WILSON_OK);
+    EXPECT(allocated == base);
+    EXPECT(wilson_dslash(out, in, U, 0.1, small, 2) == WILSON_OK);
+    EXPECT(allocated == base + links + planes);
+    limit = base + links + wilson_footprint_bytes(small, 1, nullptr);
+    iterated = false;
+    EXPECT(wilson_solve(out, in, U, 0.1, small, 1e-8, 100) == WILSON_OK);
+    EXPECT(allocated == limit);
+    EXPECT(wilson_dslash(out, in, U, 0.1, small, 2) == WILSON_OUT_OF_MEMORY);  // (the solve's workspace stays)
+    limit = ~size_t(0);
+    EXPECT(wilson_dslash(out, in, U, 0.1, small, 2) == WILSON_OK);
+    wilson_ctx *ctx = nullptr;
+    wilson_gauge *g = nullptr;
+    EXPECT(wilson_context_create(&ctx, nullptr) == WILSON_OK);
+    limit = allocated;
+    EXPECT(wilson_gauge_load(ctx, &g, U, small, 0) == WILSON_OK);  // takes what the plain calls hold
+    limit = ~size_t(0);
+    count.clear();
+    EXPECT(wilson_dslash(out, in, U, 0.1, small, 2) == WILSON_OK && count["pack"] == 1);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> all = {{"operator_order", operator_order},
                                                    {"one_launch_lost", one_launch_lost},
@@ -379,7 +407,8 @@ int main(int argc, char **argv) {
                                                    {"one_launch_room", one_launch_room},
                                                    {"load_allocates_once", load_allocates_once},
                                                    {"shape_changes", shape_changes},
-                                                   {"timed_calls", timed_calls}};
+                                                   {"timed_calls", timed_calls},
+                                                   {"plain_memory", plain_memory}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) return 2;
     it->second();

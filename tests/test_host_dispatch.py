@@ -61,3 +61,7 @@ def test_a_shape_tuned_during_a_solve_does_not_fail_it(program):
 
 def test_timed_calls_run_the_hop(program):
     run(program, "timed_calls")
+
+
+def test_plain_calls_give_back_what_they_keep(program):
+    run(program, "plain_memory")
