@@ -44,17 +44,20 @@ __device__ __forceinline__ void as_stored(Cx<R> (&o)[12]) {
     }
 }
 
-// o + y as the hop's epilogue forms it: there o is rounded before a branch that adds y; here the
-// compiler would fuse the product that made o into the sum, and FP32 and FP16 results would
-// change in their last bits with the kernel (FP64 keeps the fused form).
-template <int SP, typename R>
-__device__ __forceinline__ void add_term(Cx<R> (&o)[12], const Cx<R> (&y)[12]) {
-#pragma unroll
-    for (int k = 0; k < 12; k++) {
-        if constexpr (SP != P64) asm volatile("" : "+v"(o[k].re), "+v"(o[k].im));
-        o[k] = cadd(o[k], y[k]);
-    }
+// o + y as the hop's epilogue forms it, so that FP32 and FP16 results do not change in their last
+// bits with the kernel: there the product that made o is rounded before a branch that adds y; here
+// the compiler would fuse it into the sum (FP64 keeps that).  pinned: FP16's product with the site's
+// scale, which made y, is fused, as in the hops that load y where they add it; with plain it is
+// not, as in the direction split, which has y loaded before.
+template <typename R>
+__device__ __forceinline__ Cx<R> add_pinned(Cx<R> o, Cx<R> y) {
+    if constexpr (sizeof(R) == 4) asm volatile("" : "+v"(o.re), "+v"(o.im));
+    return cadd(o, y);
 }
+__device__ __forceinline__ Cx<double> add_plain(Cx<double> o, Cx<double> y) { return cadd(o, y); }
+#pragma clang fp contract(off)
+__device__ __forceinline__ Cx<float> add_plain(Cx<float> o, Cx<float> y) { return {o.re + y.re, o.im + y.im}; }
+#pragma clang fp contract(fast)
 
 constexpr int kCanonRow = 13;  // padded LDS row of one site: 12 complex and one unused
 
@@ -95,8 +98,7 @@ dslash_full_kernel(const FullArgs p, const VisitOrder vo) {
 #pragma unroll
     for (int s = 0; s < 4; s++)
 #pragma unroll
-        for (int k = 0; k < 3; k++) o[s * 3 + k] = cscale(acc[0][s][k], cH);
-    add_term<SP>(o, y);
+        for (int k = 0; k < 3; k++) o[s * 3 + k] = add_pinned(cscale(acc[0][s][k], cH), y[s * 3 + k]);
     as_stored<SP, R>(o);
     if (l < n) {
 #pragma unroll
@@ -160,7 +162,8 @@ dslash_rhs_kernel(const FullArgs p, int par, int has_y, const VisitOrder vo) {
     if (has_y) {
         Cx<R> y[12];
         load_site<SP, R, true>(y, fp, g.stride, rhs, i);
-        add_term<SP>(o, y);
+#pragma unroll
+        for (int k = 0; k < 12; k++) o[k] = add_pinned(o[k], y[k]);
     }
     as_stored<SP, R>(o);
     if constexpr (LL) __syncthreads();  // every wave has read the links
@@ -290,8 +293,8 @@ __global__ void __launch_bounds__(320) dslash_small_kernel(const FullArgs p) {
                          ((part[0][2 * k + 1][lane] + part[1][2 * k + 1][lane]) + part[2][2 * k + 1][lane]) +
                              part[3][2 * k + 1][lane]};
         o[k] = cscale(t, cH);
+        if (p.par == 2) o[k] = add_plain(o[k], y[k]);
     }
-    if (p.par == 2) add_term<SP>(o, y);
     as_stored<SP, R>(o);
     if (!valid) return;
     dvec2 *dst = reinterpret_cast<dvec2 *>(p.out) + ((size_t)rhs * g.Vh * 2 + 2 * (size_t)i + c.b) * 12;

@@ -1,0 +1,53 @@
+"""FP32 and FP16 results of the operator call do not change with the kernel: the call's own kernels
+against the hops whose order of additions they keep (pinned launch shapes between conversions), bit
+for bit.  Run with tuning off in a process of its own, so that no tuned shape decides the route."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+DRIVER = r'''
+import os, sys
+import torch
+from paper_1811_00893_amd import _lib as L, inputs
+dev = torch.device("cuda:0")
+PLAIN, SPLIT = "256,1,1,0", "320,1,1,0,0,0,0,1"
+# below 4096 sites per parity (canonical input, direction split); above (planes, plain order), ragged
+for dims in ((2, 2, 2, 2), (4, 6, 8, 10), (8, 8, 8, 8), (16, 8, 8, 16), (18, 10, 14, 22)):
+    U = inputs.gauge_field(dims, eps=0.3, seed=4900, device=dev)
+    small = dims[0] * dims[1] * dims[2] * dims[3] < 8192
+    for scale in (1.0, 1.25):  # 1.25 U is not SU(3): links kept in full
+        for nrhs in (1, 2, 3, 5, 12):
+            psi = inputs.gaussian_source(dims, seed=4901, nrhs=nrhs, device=dev)
+            for prec in (1, 2, 3) if scale == 1.0 else (1,):
+                out = []
+                for shape in (None, SPLIT if small else PLAIN):
+                    os.environ.pop("WILSON_HOP_CFG", None)
+                    if shape:
+                        os.environ["WILSON_HOP_CFG"] = shape
+                    ctx = L.wilson_context_create()
+                    g = L.wilson_gauge_load(ctx, scale * U, dims, 7)
+                    for parity in (2, 0, 1):
+                        o = torch.zeros_like(psi)
+                        L.check(L.wilson_dslash_ex(ctx, g, o, psi, 0.124, parity, prec, nrhs), "dslash")
+                        torch.cuda.synchronize()
+                        out.append(o)
+                    L.wilson_gauge_free(ctx, g)
+                    L.wilson_context_destroy(ctx)
+                for parity, own, hop in zip((2, 0, 1), out[:3], out[3:]):
+                    if not torch.equal(own, hop):
+                        print("differ:", dims, "scale", scale, "nrhs", nrhs, "precision", prec, "parity", parity)
+    print("compared", dims, flush=True)
+'''
+
+
+def test_own_kernels_have_the_bits_of_the_hop():
+    env = {k: v for k, v in os.environ.items() if not k.startswith("WILSON_")}
+    r = subprocess.run([sys.executable, "-u", "-c", DRIVER], cwd=ROOT, env=dict(env, WILSON_TUNE="0"), capture_output=True,
+                       text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert r.stdout.count("compared") == 5 and "differ" not in r.stdout, r.stdout[-4000:]
