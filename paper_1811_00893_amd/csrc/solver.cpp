@@ -1244,8 +1244,8 @@ void dslash_device(wilson_ctx *ctx, const wilson_gauge *G, double *out, const do
     else WL_HIP(launch_split_one(ws->in[1 - parity].f, in, g, 1 - parity, nrhs, ctx->stream));
     // D on one right-hand side in one launch, and hops of several that write the canonical layout
     // themselves (one parity of 12 FP32 RHS at 24^3x48: 628 us against 727 through the hop's
-    // planes).  FP32 and FP16 fields keep to the hop where its tuned shape adds the directions in
-    // another order (as for the small kernel).
+    // planes).  FP32 and FP16 fields keep to the hop where its tuned shape gives other bits (as for
+    // the small kernel): it adds the directions in another order, or rounds rebuilt links to FP16.
     a.par = parity == 2 ? 0 : parity;
     a.out = ws->out[a.par].f;
     a.in = ws->in[1 - a.par].f;
@@ -1253,7 +1253,7 @@ void dslash_device(wilson_ctx *ctx, const wilson_gauge *G, double *out, const do
     bool canon = own && (nrhs > 1 || parity == 2);
     if (canon && P != P64) {
         const LaunchCfg c = hop_config(ctx, a);
-        canon = !c.dsplit && !c.tm;
+        canon = !c.dsplit && !c.tm && !(c.ldsl == 2 && GP == P16);
     }
     if (canon) {
         f.f[0] = ws->in[0].f;

@@ -237,6 +237,13 @@ static void operator_order() {
         EXPECT(p.dslash(2, WILSON_FP64) == WILSON_OK);  // FP64 always takes its own kernel
         EXPECT(count["hop"] == 0 && count["full"] + count["small"] == 1);
     }
+    favourite = [](const LaunchCfg &c) { return c.ldsl == 2; };  // FP16 links rebuilt and rounded again
+    Problem p(8, 8, 16, 32, 12);
+    for (int precision : {WILSON_FP32, WILSON_FP16, WILSON_FP16_L32}) {
+        EXPECT(p.dslash(1, precision, 12) == WILSON_OK);
+        EXPECT(p.dslash(1, precision, 12) == WILSON_OK);
+        EXPECT(count["hop"] == (precision == WILSON_FP16) && count["rhs"] == (precision != WILSON_FP16));
+    }
 }
 
 // A one-launch solve that is refused, or whose blocks lose each other (also where the state looks
