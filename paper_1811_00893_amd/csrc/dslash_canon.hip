@@ -328,13 +328,17 @@ template <int SP, int GP, int NE>
 static hipError_t rhs_pgn(const FullArgs &p, int par, int has_y, hipStream_t s) {
     constexpr bool SHX = SP != P64;
     constexpr size_t turn = 64 * kCanonRow * 2 * sizeof(real_t<SP>);  // one wave's
-    // t visited inside eighths of z (24^3x48, 12 RHS in FP32: 606 us, against 619 for quarters, 626 for
-    // twelfths and 630 in plain order)
+    // t visited inside eighths of z where a z-plane is whole tiles of 64 sites, memory order
+    // elsewhere.  What it is worth depends on size and count, either way by less than a tenth (us, 12 RHS,
+    // one parity, eighths / memory order): 32^4 FP64 1435 / 1470, FP32 1011 / 1016; 16^3x32 FP64 145 / 145, FP32
+    // 116 / 105.  Ragged planes gain on large lattices only: 24^3x48 FP64 829 / 872, FP32 608 / 630, but
+    // 18x10x16x22 FP64 79 / 77, FP32 61 / 57.
     const int zblk = p.g.L[2] % 8 == 0 && (p.g.Lxh * p.g.L[1]) % 64 == 0 ? p.g.L[2] / 8 : 0;
     // Links in LDS for 4 or 3 right-hand sides at a time: at 24^3x48 one parity of 12 takes 631 us
     // against 687 without in FP32 and 881 against 954 in FP64, with the conversion.  Two at a time do
     // not repay the barriers (109 against 103 us in FP32), nor do FP16's short loads (569 against
-    // 566); whole links (18 reals) take the registers or the LDS (FP32 1141 against 746).
+    // 566); 5, 7 or 11 divide into no such group (5 at 24^3x48: FP32 292 us, 510 through the hop's planes;
+    // FP64 412 / 712); whole links (18 reals) take the registers or the LDS (FP32 1141 against 746).
     if constexpr (SP != P16 && NE == 6) {
         const int nw = p.nrhs % 4 == 0 ? 4 : (p.nrhs % 3 == 0 ? 3 : 1);
         if (nw > 1) {

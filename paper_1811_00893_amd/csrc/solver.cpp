@@ -538,13 +538,17 @@ class EoCore : public EoMem {
             a.a = p.f; a.b = s.f;
             run_blas(BL_COPY_NORM, a, vec_bytes(P, 2));
         }
-        // Enqueue iterations ahead of the host, which polls `lag` iterations behind the newest but
-        // one.  The iterations in flight when the solve converges run masked, but still launch
-        // (11 kernels, 5-25 us each with the lattice's blocks); with none behind, the GPU waits a few us
-        // for the host after each iteration.  Whole solves, ms, lag 0 / 1 / 2, by the bytes of 20
-        // vectors: CGNR 20x12x28x36 FP64 (0.46 GB) 12.5 / 12.1 / 12.1, clover 24^3x48 FP32 inner
-        // (0.64) 12.18 / 11.96 / 12.04, 32^3x64 FP64 (4.0) 41.3 / 41.2 / 41.25, 24^3x48 FP32 inner with
-        // 12 RHS (7.6) 62.8 / 63.0 / 63.5.
+        // Enqueue iterations ahead of the host, which polls `lag` iterations behind the newest.  The
+        // iterations in flight when the solve converges run masked, but still launch (11 kernels,
+        // 5-25 us each with the lattice's blocks); with none behind, the GPU waits a few us for the
+        // host after each iteration.  Whole solves, ms, lag 0 / 1 / 2, by the bytes of 20 vectors in GB:
+        //   FP64        16^3x32 (0.25) 3.84 / 3.64 / 3.67, 24^3x48 (1.3) 14.55 / 14.35 / 14.40, 32^3x64 (4.0) 39.99 /
+        //               39.84 / 39.86, 40^3x64 (7.9) 83.78 / 83.62 / 83.78; CGNR 20x12x28x36 (0.46) 12.5 / 12.1 / 12.1,
+        //               24^3x48 29.5 / 29.0 / 29.1; clover 24^3x48 20.82 / 20.61 / 20.64
+        //   FP32 inner  24^3x48 (0.64) 8.95 / 8.81 / 8.89, with clover 11.98 / 11.85 / 11.94, 4 RHS (2.5) 23.37 / 23.32 /
+        //               23.59, 12 RHS (7.6) 62.67 / 62.84 / 63.30; 48^3x96 (10.2) 110.0 / 110.1 / 110.4
+        //   FP16 inner  32^3x64 (1.1) 20.84 / 20.73 / 20.95, 48^3x64 (3.7) 65.99 / 66.00 / 66.41
+        // So one behind is best or within 0.3 % of it everywhere, and where the lines lie matters little.
         const double size = vec_bytes(P, 20);
         const int lag = size > 6e9 ? 0 : (size > 6e8 ? 1 : 2);
         int it = 0;
@@ -590,8 +594,8 @@ class EoCore : public EoMem {
     // and whose partial rows one wave sums, FP64 or FP32, no clover term, no more blocks than CUs,
     // nothing asked for that needs the separate launches (per-launch timing, graphs, separate
     // finalizes).  8^4 FP64: 58 us per iteration in nine launches, 32 in one; whole solves, us,
-    // separate launches against one: 8^4 FP64 1 RHS 1230 / 763, 8 RHS 1353 / 895, mixed FP32
-    // 1519 / 887; 8^2x16^2 (128 tiles) FP64 1478 / 1180, mixed 1596 / 1116.
+    // separate launches / one: 8^4 FP64 1 RHS 1182 / 725, 8 RHS 1317 / 845, mixed FP32 1395 / 821;
+    // 8^2x16^2 (128 tiles) FP64 1415 / 1214, mixed 1446 / 1093.
     int small_cus() {
         int &cus = ctx->small_blocks[P == P64 ? 0 : 1][G->recon == 12 ? 0 : 1];
         if (cus < 0) cus = small_max_blocks(P, G->recon);
