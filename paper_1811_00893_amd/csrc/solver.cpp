@@ -71,8 +71,8 @@ static bool prefin_enabled() {
 }
 
 // The one-launch BiCGStab of small lattices: polls after which a block gives up waiting for the
-// others.  2^21 polls take a second or two, far beyond any wait for blocks that other work on
-// the device holds up and short enough to be lost now and then; 0 turns the one-launch solve off.
+// others.  2^21 polls take a second or two: longer than other work on the device usually holds
+// blocks up, short enough to be lost now and then; 0 turns the one-launch solve off.
 static unsigned one_launch_spins() {
     const char *e = std::getenv("WILSON_ONE_LAUNCH");
     if (!e || !*e) return 1u << 21;
@@ -81,7 +81,7 @@ static unsigned one_launch_spins() {
 
 // Room on each device for the blocks of one-launch solves, which wait for each other: those of all
 // contexts in flight stay within the CUs.  Blocks are dealt to the 8 XCDs in turn, so a solve
-// counts with whole rounds and no XCD is asked for more than its share.  Held until the host has
+// counts as a multiple of 8 and no XCD is asked for more than its share.  Held until the host has
 // waited for the launch; a solve that finds no room takes the separate launches.
 struct SmallRoom {
     static constexpr int kDevices = 64;

@@ -10,7 +10,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-DRIVER = r'''
+SCRIPT = r'''
 import os, sys
 import torch
 from paper_1811_00893_amd import _lib as L, inputs
@@ -47,7 +47,7 @@ for dims in ((2, 2, 2, 2), (4, 6, 8, 10), (8, 8, 8, 8), (16, 8, 8, 16), (18, 10,
 
 def test_own_kernels_have_the_bits_of_the_hop():
     env = {k: v for k, v in os.environ.items() if not k.startswith("WILSON_")}
-    r = subprocess.run([sys.executable, "-u", "-c", DRIVER], cwd=ROOT, env=dict(env, WILSON_TUNE="0"), capture_output=True,
+    r = subprocess.run([sys.executable, "-u", "-c", SCRIPT], cwd=ROOT, env=dict(env, WILSON_TUNE="0"), capture_output=True,
                        text=True, timeout=100)
     assert r.returncode == 0, r.stderr[-2000:]
     assert r.stdout.count("compared") == 5 and "differ" not in r.stdout, r.stdout[-4000:]
